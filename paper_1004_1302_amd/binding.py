@@ -292,6 +292,7 @@ def get_workspace(nbytes: int, device):
     t = _ws_cache.get(key)
     if t is None or t.numel() < nbytes:
         _ws_cache.pop(key, None)
+        t = None  # the old buffer goes before the larger one comes
         t = torch.empty(max(nbytes, 256), dtype=torch.uint8, device=device)
         _ws_cache[key] = t
     assert t.data_ptr() % 256 == 0
