@@ -42,7 +42,7 @@ struct SpeciesDev {
 //   a.x = i0 | i1 << 14 | species << 28     a.y = j0 | j1 << 14
 //   a.z = float(u - i0)                     a.w = float(v - j0)
 //   b.x = float((f sigma_s)^2)              b.y = float(log2(e) / sigma_s^2)
-//   b.z = value (raw scalar)                b.w = rho0
+//   b.z = value, or its log10 (colour_scale) b.w = rho0
 struct Rec {
     uint4 a, b;
 };
@@ -281,21 +281,28 @@ __host__ __device__ inline uint32_t from_order_bits_u(uint32_t k) {
 // Normalised scalar t in [0, 1] (Section 3.2: values are normalised before
 // colouring): (g(v) - g(vmin)) / (g(vmax) - g(vmin)) clamped, g = log10 or
 // the identity; t = 0 for non-positive values under log10 or an empty range.
-__device__ __forceinline__ float normalise_value(float v, float vmin, float vmax, int log_scale) {
-    float gv, g0, g1;
-    if (log_scale) {
-        if (!(v > 0.0f) || !(vmin > 0.0f) || !(vmax > 0.0f)) return 0.0f;
-        gv = log10f(v);
-        g0 = log10f(vmin);
-        g1 = log10f(vmax);
-    } else {
-        gv = v;
-        g0 = vmin;
-        g1 = vmax;
-    }
-    float den = g1 - g0;
-    if (!(den > 0.0f)) return 0.0f;
-    float t = (gv - g0) / den;
+// In three parts, each done where it is done least often: g(v) once per
+// particle by the projection (into the record), g of the range once per
+// workgroup by the splat, and the quotient wherever a record is staged.
+__device__ __forceinline__ float colour_scale(float v, int log_scale) {
+    if (!log_scale) return v;
+    return v > 0.0f ? log10f(v) : -__builtin_inff();
+}
+
+struct ColourRange {
+    float g0, den;  // g(vmin), g(vmax) - g(vmin); den <= 0 (or NaN): t = 0
+};
+
+__device__ __forceinline__ ColourRange colour_range(float vmin, float vmax, int log_scale) {
+    if (!log_scale) return {vmin, vmax - vmin};
+    if (!(vmin > 0.0f) || !(vmax > 0.0f)) return {0.0f, 0.0f};
+    const float g0 = log10f(vmin);
+    return {g0, log10f(vmax) - g0};
+}
+
+__device__ __forceinline__ float normalise_value(float gv, ColourRange r) {
+    if (!(r.den > 0.0f)) return 0.0f;
+    const float t = (gv - r.g0) / r.den;
     return fminf(fmaxf(t, 0.0f), 1.0f);
 }
 

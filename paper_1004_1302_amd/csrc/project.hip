@@ -244,7 +244,7 @@ __global__ __launch_bounds__(kThreads) void k_project(ProjectArgs a) {
             r.a.w = __float_as_uint(p.vr);
             r.b.x = __float_as_uint(p.r2);
             r.b.y = __float_as_uint(qsf);
-            r.b.z = __float_as_uint(v);
+            r.b.z = __float_as_uint(colour_scale(v, a.sp.log_scale[sp]));
             r.b.w = __float_as_uint(r0);
             a.rec[k] = r;
             if (!a.tile_mask) {
