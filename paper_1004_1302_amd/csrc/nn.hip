@@ -8,6 +8,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "nn_internal.h"
 
 namespace splotch {
@@ -227,6 +229,213 @@ __global__ __launch_bounds__(256) void k_conv3x3(const bf16_t *x, const bf16_t *
     }
 }
 
+// Adjoint weights: wf[ci][9 cout], the forward operand w[9 cin][cout] with
+// its taps mirrored and channels swapped, so that backward-data is the same
+// convolution of dZ (cout channels in, cin out).
+__global__ void k_conv_wf_adjoint(const bf16_t *w, bf16_t *wf, int cin, int cout) {
+    const int k9 = 9 * cout, total = k9 * cin;
+    for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < total; e += gridDim.x * blockDim.x) {
+        const int ci = e / k9, k = e % k9, tap = k / cout, co = k % cout;
+        wf[e] = w[((size_t)(8 - tap) * cin + ci) * cout + co];
+    }
+}
+
+// The convolution with its reduction in tap-major order (tap, then input
+// channels) for inputs of several 32-channel slices: the order in which
+// backward-data sums.  All slices of the halo tile are staged at once and
+// the weights a tap at a time.  SL: slices the tile holds (cin <= 32 SL).
+template <int SL>
+__global__ __launch_bounds__(256) void k_conv3x3_taps(const bf16_t *x, const bf16_t *wf,
+                                                      float *out, int h, int w, int cin,
+                                                      int cout) {
+    constexpr int NT = 2;  // 32 output channels
+    constexpr int ROW = SL * kCK + PAD;
+    __shared__ __attribute__((aligned(16))) bf16_t sX[kCHP][ROW];
+    __shared__ __attribute__((aligned(16))) bf16_t sW[2][32][ROW];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tiles_x = (w + kCTW - 1) / kCTW, tiles_y = (h + kCTH - 1) / kCTH;
+    const int tile = (int)(blockIdx.x % (unsigned)(tiles_x * tiles_y));
+    const int img = (int)(blockIdx.x / (unsigned)(tiles_x * tiles_y));
+    const int y0 = (tile / tiles_x) * kCTH, x0 = (tile % tiles_x) * kCTW;
+    const int n0 = (int)blockIdx.y * 32;
+    const size_t k9 = (size_t)9 * cin, plane = (size_t)img * h;
+    const int c8 = cin / 8;
+    for (int e = tid; e < kCHP * c8; e += 256) {
+        const int p = e / c8, q = (e % c8) * 8;
+        const int yy = y0 - 1 + p / kCHW, xx = x0 - 1 + p % kCHW;
+        uint4 v = make_uint4(0u, 0u, 0u, 0u);
+        if (yy >= 0 && yy < h && xx >= 0 && xx < w)
+            v = *reinterpret_cast<const uint4 *>(x + ((plane + yy) * w + xx) * cin + q);
+        *reinterpret_cast<uint4 *>(&sX[p][q]) = v;
+    }
+    auto stage_w = [&](int tap) {
+        for (int e = tid; e < 32 * c8; e += 256) {
+            const int r = e / c8, q = (e % c8) * 8;
+            *reinterpret_cast<uint4 *>(&sW[tap & 1][r][q]) = *reinterpret_cast<const uint4 *>(
+                wf + (size_t)(n0 + r) * k9 + (size_t)tap * cin + q);
+        }
+    };
+    f32x4 acc[2][NT];
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < NT; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int kq = (lane >> 4) * 8;
+    stage_w(0);
+    __syncthreads();
+    for (int tap = 0; tap < 9; ++tap) {
+        // the next tap's weights into the half that the tap before used
+        if (tap + 1 < 9) stage_w(tap + 1);
+        const int dy = tap / 3, dx = tap % 3;
+        for (int c0 = 0; c0 < cin; c0 += kCK) {
+            bf16x8 af[2], bfr[NT];
+#pragma unroll
+            for (int a = 0; a < 2; ++a)
+                af[a] = *reinterpret_cast<const bf16x8 *>(
+                    &sX[(2 * wave + a + dy) * kCHW + (lane & 15) + dx][c0 + kq]);
+#pragma unroll
+            for (int b = 0; b < NT; ++b)
+                bfr[b] = *reinterpret_cast<const bf16x8 *>(
+                    &sW[tap & 1][b * 16 + (lane & 15)][c0 + kq]);
+#pragma unroll
+            for (int a = 0; a < 2; ++a)
+#pragma unroll
+                for (int b = 0; b < NT; ++b)
+                    acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[a], bfr[b], acc[a][b],
+                                                                        0, 0, 0);
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int a = 0; a < 2; ++a) {
+        const int yy = y0 + 2 * wave + a;
+        if (yy >= h) continue;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int xx = x0 + (lane >> 4) * 4 + q;
+            if (xx >= w) continue;
+#pragma unroll
+            for (int b = 0; b < NT; ++b)
+                out[((plane + yy) * w + xx) * cout + n0 + b * 16 + (lane & 15)] = acc[a][b][q];
+        }
+    }
+}
+
+// ------------------------------------------------------- weight gradient
+// part[s][tap][ci][co] = sum over the pixels p of split s of
+// x[p shifted by tap][ci] dz[p][co], without an im2col buffer: the
+// reduction runs over pixels, so both MFMA operands are wanted
+// channel-major.  A workgroup stages 8 x 32 pixel tiles of 32 channels of dz
+// and, with the one-pixel halo, of x in LDS as they lie in memory, and
+// ds_read_b64_tr_b16 transposes on the way to the registers (16 lanes read
+// four pixels x 16 channels; lane l gets channel l of the four), so a tap's
+// shift is a row offset.  Each of the four waves owns 16 x 16 channels and
+// all nine taps (36 accumulator registers); an input row's three fragments
+// serve three output rows.  The halves of a row are swapped for pixels with
+// bit 3 set: the 32 lanes of a transposed read then meet distinct LDS banks.
+// Bound by reading x and dz once per 32 x 32 channel block (0.54 GB, 0.11 ms
+// at a copy's rate, on four 1024 x 1024 images of 32 channels): 0.24 ms
+// there and 0.48 ms for 64 to 32 channels, where im2col and a split-K GEMM
+// with transposing element loads took 2.73 and 7.4 ms.
+constexpr int kDTH = 8, kDTW = 32, kDHW = kDTW + 2;
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef short s16x8 __attribute__((ext_vector_type(8)));
+
+__device__ __forceinline__ int dw_at(int p, int c) { return p * 32 + (c ^ ((p & 8) << 1)); }
+
+// Eight consecutive pixels (from p) of channel c0 + lane % 16, p including
+// this lane's 8 (lane / 16).
+__device__ __forceinline__ bf16x8 read_tr8(const bf16_t *s, int p, int c0, int lane) {
+    typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+    const int r = (lane & 15) >> 2, c = c0 + (lane & 3) * 4;
+    const s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(s + dw_at(p + r, c)));
+    const s16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(s + dw_at(p + 4 + r, c)));
+    const s16x8 v = __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
+    return __builtin_bit_cast(bf16x8, v);
+}
+
+__global__ __launch_bounds__(256) void k_conv3x3_dw(const bf16_t *x, const bf16_t *dz, float *part,
+                                                    int n, int h, int w, int cin, int cout) {
+    __shared__ __attribute__((aligned(16))) bf16_t sX[(kDTH + 2) * kDHW * 32];
+    __shared__ __attribute__((aligned(16))) bf16_t sZ[kDTH * kDTW * 32];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int cb = cin / 32, ci0 = (int)(blockIdx.y % (unsigned)cb) * 32,
+              co0 = (int)(blockIdx.y / (unsigned)cb) * 32;
+    const int mi = (wave & 1) * 16, ni = (wave >> 1) * 16;
+    const int tiles_x = (w + kDTW - 1) / kDTW, tiles_y = (h + kDTH - 1) / kDTH;
+    const long long tiles = (long long)tiles_x * tiles_y * n;
+    const long long per = (tiles + gridDim.x - 1) / gridDim.x;
+    const long long t0 = per * blockIdx.x, t1 = t0 + per < tiles ? t0 + per : tiles;
+    f32x4 acc[9];
+#pragma unroll
+    for (int t = 0; t < 9; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int g8 = (lane >> 4) * 8;
+    for (long long t = t0; t < t1; ++t) {
+        const int img = (int)(t / (tiles_x * tiles_y)), tt = (int)(t % (tiles_x * tiles_y));
+        const int y0 = (tt / tiles_x) * kDTH, x0 = (tt % tiles_x) * kDTW;
+        const size_t plane = (size_t)img * h;
+        __syncthreads();  // the previous tile's fragments are read
+        for (int e = tid; e < (kDTH + 2) * kDHW * 4; e += 256) {
+            const int p = e >> 2, q = (e & 3) * 8;
+            const int yy = y0 - 1 + p / kDHW, xx = x0 - 1 + p % kDHW;
+            uint4 v = make_uint4(0u, 0u, 0u, 0u);
+            if (yy >= 0 && yy < h && xx >= 0 && xx < w)
+                v = *reinterpret_cast<const uint4 *>(x + ((plane + yy) * w + xx) * cin + ci0 + q);
+            *reinterpret_cast<uint4 *>(&sX[dw_at(p, q)]) = v;
+        }
+        for (int e = tid; e < kDTH * kDTW * 4; e += 256) {
+            const int p = e >> 2, q = (e & 3) * 8;
+            const int yy = y0 + p / kDTW, xx = x0 + p % kDTW;
+            uint4 v = make_uint4(0u, 0u, 0u, 0u);
+            if (yy < h && xx < w)
+                v = *reinterpret_cast<const uint4 *>(dz + ((plane + yy) * w + xx) * cout + co0 + q);
+            *reinterpret_cast<uint4 *>(&sZ[dw_at(p, q)]) = v;
+        }
+        __syncthreads();
+        bf16x8 af[3][3];  // input row (mod 3), tap column
+#pragma unroll
+        for (int r = 0; r < 2; ++r)
+#pragma unroll
+            for (int dx = 0; dx < 3; ++dx) af[r][dx] = read_tr8(sX, r * kDHW + dx + g8, mi, lane);
+#pragma unroll
+        for (int r = 0; r < kDTH; ++r) {
+            const bf16x8 bf = read_tr8(sZ, r * kDTW + g8, ni, lane);
+#pragma unroll
+            for (int dx = 0; dx < 3; ++dx)
+                af[(r + 2) % 3][dx] = read_tr8(sX, (r + 2) * kDHW + dx + g8, mi, lane);
+#pragma unroll
+            for (int tap = 0; tap < 9; ++tap)
+                acc[tap] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[(r + tap / 3) % 3][tap % 3],
+                                                                   bf, acc[tap], 0, 0, 0);
+        }
+    }
+#pragma unroll
+    for (int tap = 0; tap < 9; ++tap)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int ci = ci0 + mi + (lane >> 4) * 4 + q, co = co0 + ni + (lane & 15);
+            part[(((size_t)blockIdx.x * 9 + tap) * cin + ci) * cout + co] = acc[tap][q];
+        }
+}
+
+// out[e] = sum of part[s][e] over the splits: 64 values a workgroup, each
+// summed by 16 threads (a thread per value took 62 us for 256 splits).
+__global__ __launch_bounds__(1024) void k_sum_splits(const float *part, int splits, size_t mn,
+                                                     float *out) {
+    __shared__ float sh[16][64];
+    const size_t e = (size_t)blockIdx.x * 64 + (threadIdx.x & 63);
+    const int g = threadIdx.x >> 6;
+    float v = 0.f;
+    if (e < mn)
+        for (int z = g; z < splits; z += 16) v += part[(size_t)z * mn + e];
+    sh[g][threadIdx.x & 63] = v;
+    __syncthreads();
+    if (g == 0 && e < mn) {
+        for (int k = 1; k < 16; ++k) v += sh[k][threadIdx.x];
+        out[e] = v;
+    }
+}
+
 // ------------------------------------------------------------------ im2col
 // out[p][tap*C + c] = in[p shifted by tap][c] (zero outside the image),
 // taps in (ky, kx) row-major order, p = (img, y, x).
@@ -274,9 +483,8 @@ __global__ void k_epilogue(const float *Cp, int splits, size_t mn, int n, const 
     }
 }
 
-// dZ = dY * [Y > 0] (ReLU adjoint), written as BF16 for the GEMMs and
-// reduced per channel into the bias gradient (one atomic per block and
-// channel is avoided: per-block partial sums, reduced by k_colsum).
+// dZ = dY * [Y > 0] (ReLU adjoint), written as BF16 for the GEMMs (and as
+// FP32 where asked for).
 __global__ void k_relu_bwd(const float *dy, const bf16_t *y, int relu, bf16_t *dz_bf,
                            float *dz_f, size_t total) {
     size_t stride = (size_t)gridDim.x * blockDim.x;
@@ -285,6 +493,53 @@ __global__ void k_relu_bwd(const float *dy, const bf16_t *y, int relu, bf16_t *d
         if (relu && !(bf2f(y[e]) > 0.f)) g = 0.f;
         dz_bf[e] = f2bf(g);
         if (dz_f) dz_f[e] = g;
+    }
+}
+
+// The same for [rows][cols] with the bias gradient's per-block column sums
+// of the FP32 dZ (part, as k_colsum_part's) taken on the way, four channels
+// a thread: dZ in FP32 need not be written and read again.  cols is a
+// multiple of 4, at most 256; y may be null (no ReLU).
+__global__ __launch_bounds__(256) void k_relu_bwd_bias(const float *dy, const bf16_t *y,
+                                                       size_t rows, int cols,
+                                                       size_t rows_per_block, bf16_t *dz_bf,
+                                                       float *part) {
+    __shared__ float4 sh[256];
+    const int c4 = cols / 4, per_row = 256 / c4;
+    const int t = threadIdx.x, c = t % c4, r0 = t / c4;
+    const size_t beg = (size_t)blockIdx.x * rows_per_block;
+    const size_t end = beg + rows_per_block < rows ? beg + rows_per_block : rows;
+    float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (r0 < per_row)
+        for (size_t r = beg + r0; r < end; r += per_row) {
+            const size_t e = r * cols + 4 * c;
+            float4 g = *reinterpret_cast<const float4 *>(dy + e);
+            if (y) {
+                const ushort4 v = *reinterpret_cast<const ushort4 *>(y + e);
+                if (!(bf2f(v.x) > 0.f)) g.x = 0.f;
+                if (!(bf2f(v.y) > 0.f)) g.y = 0.f;
+                if (!(bf2f(v.z) > 0.f)) g.z = 0.f;
+                if (!(bf2f(v.w) > 0.f)) g.w = 0.f;
+            }
+            *reinterpret_cast<ushort4 *>(dz_bf + e) =
+                make_ushort4(f2bf(g.x), f2bf(g.y), f2bf(g.z), f2bf(g.w));
+            s.x += g.x;
+            s.y += g.y;
+            s.z += g.z;
+            s.w += g.w;
+        }
+    sh[t] = s;
+    __syncthreads();
+    if (t < c4) {
+        float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int k = 0; k < per_row; ++k) {
+            const float4 v = sh[k * c4 + t];
+            a.x += v.x;
+            a.y += v.y;
+            a.z += v.z;
+            a.w += v.w;
+        }
+        *reinterpret_cast<float4 *>(part + (size_t)blockIdx.x * cols + 4 * t) = a;
     }
 }
 
@@ -310,12 +565,15 @@ __global__ void k_colsum_part(const float *in, size_t rows, int cols, size_t row
     }
 }
 
-__global__ void k_colsum_final(const float *part, int nblocks, int cols, float *out) {
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= cols) return;
+// One wave per column adds its partials (a thread per column took 230 us
+// for 1024 partials).
+__global__ __launch_bounds__(64) void k_colsum_final(const float *part, int nblocks, int cols,
+                                                     float *out) {
+    const int c = blockIdx.x;
     float s = 0.f;
-    for (int b = 0; b < nblocks; ++b) s += part[(size_t)b * cols + c];
-    out[c] = s;
+    for (int b = threadIdx.x; b < nblocks; b += 64) s += part[(size_t)b * cols + c];
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+    if (threadIdx.x == 0) out[c] = s;
 }
 
 // 2x2 average pool (NHWC, BF16 in/out) and its adjoint (FP32 in/out).
@@ -575,6 +833,63 @@ hipError_t conv3x3(const bf16_t *x, const bf16_t *wf, const float *bias, int rel
     return hipGetLastError();
 }
 
+hipError_t conv3x3_adjoint_weights(const bf16_t *w, bf16_t *wf, int cin, int cout,
+                                   hipStream_t s) {
+    hipLaunchKernelGGL(k_conv_wf_adjoint, dim3(grid_for((size_t)9 * cin * cout)), dim3(256), 0, s,
+                       w, wf, cin, cout);
+    return hipGetLastError();
+}
+
+hipError_t conv3x3_bwd_data(const bf16_t *dz, const bf16_t *wf, float *dx, int n, int h, int w,
+                            int cin, int cout, hipStream_t s) {
+    // one slice: the forward kernel's order is tap-major already
+    if (cout == 32)
+        return conv3x3(dz, wf, nullptr, 0, nullptr, nullptr, dx, n, h, w, cout, cin, s);
+    const unsigned tiles = (unsigned)((h + kCTH - 1) / kCTH) * (unsigned)((w + kCTW - 1) / kCTW);
+    const dim3 grid(tiles * (unsigned)n, (unsigned)(cin / 32)), block(256);
+    if (cout <= 64)
+        hipLaunchKernelGGL(k_conv3x3_taps<2>, grid, block, 0, s, dz, wf, dx, h, w, cout, cin);
+    else if (cout <= 128)
+        hipLaunchKernelGGL(k_conv3x3_taps<4>, grid, block, 0, s, dz, wf, dx, h, w, cout, cin);
+    else
+        hipLaunchKernelGGL(k_conv3x3_taps<8>, grid, block, 0, s, dz, wf, dx, h, w, cout, cin);
+    return hipGetLastError();
+}
+
+int conv3x3_dw_splits(int n, int h, int w, int cin, int cout) {
+    // about 1024 workgroups (four a CU) in all, at least a tile each
+    const uint64_t tiles =
+        (uint64_t)n * ((h + kDTH - 1) / kDTH) * (uint64_t)((w + kDTW - 1) / kDTW);
+    const uint64_t want = std::max<uint64_t>(1, 1024 / ((uint64_t)(cin / 32) * (cout / 32)));
+    return (int)std::min(tiles, want);
+}
+
+hipError_t conv3x3_dw(const bf16_t *x, const bf16_t *dz, float *part, float *dw, int n, int h,
+                      int w, int cin, int cout, hipStream_t s) {
+    const int splits = conv3x3_dw_splits(n, h, w, cin, cout);
+    hipLaunchKernelGGL(k_conv3x3_dw, dim3(splits, (cin / 32) * (cout / 32)), dim3(256), 0, s, x, dz,
+                       part, n, h, w, cin, cout);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    const size_t mn = (size_t)9 * cin * cout;
+    hipLaunchKernelGGL(k_sum_splits, dim3((unsigned)((mn + 63) / 64)), dim3(1024), 0, s, part,
+                       splits, mn, dw);
+    return hipGetLastError();
+}
+
+hipError_t relu_bwd_bias(const float *dy, const bf16_t *y, size_t rows, int cols, bf16_t *dz_bf,
+                         float *db, float *part, hipStream_t s) {
+    size_t rpb = (rows + kColsumBlocks - 1) / kColsumBlocks;
+    if (rpb < 64) rpb = 64;
+    const int nb = (int)((rows + rpb - 1) / rpb);
+    hipLaunchKernelGGL(k_relu_bwd_bias, dim3(nb), dim3(256), 0, s, dy, y, rows, cols, rpb, dz_bf,
+                       part);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_colsum_final, dim3(cols), dim3(64), 0, s, part, nb, cols, db);
+    return hipGetLastError();
+}
+
 hipError_t relu_bwd(const float *dy, const bf16_t *y, int relu, bf16_t *dz_bf, float *dz_f,
                     size_t total, hipStream_t s) {
     hipLaunchKernelGGL(k_relu_bwd, dim3(grid_for(total)), dim3(256), 0, s, dy, y, relu, dz_bf,
@@ -589,8 +904,7 @@ hipError_t colsum(const float *in, size_t rows, int cols, float *out, float *par
     hipLaunchKernelGGL(k_colsum_part, dim3(nb), dim3(256), 0, s, in, rows, cols, rpb, part);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_colsum_final, dim3((cols + 255) / 256), dim3(256), 0, s, part, nb, cols,
-                       out);
+    hipLaunchKernelGGL(k_colsum_final, dim3(cols), dim3(64), 0, s, part, nb, cols, out);
     return hipGetLastError();
 }
 

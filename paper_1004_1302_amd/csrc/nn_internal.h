@@ -21,12 +21,25 @@ hipError_t conv3x3_weights(const bf16_t *w, bf16_t *wf, int cin, int cout, hipSt
 hipError_t conv3x3(const bf16_t *x, const bf16_t *wf, const float *bias, int relu,
                    const float *residual, bf16_t *out_bf, float *out_f, int n, int h, int w,
                    int cin, int cout, hipStream_t s);
+// Backward-data of the convolution (cin -> cout): dx = conv3x3(dz, adjoint
+// weights), its reduction in (tap, output channel) order.  wf from
+// conv3x3_adjoint_weights (w: the [9 cin][cout] operand).
+hipError_t conv3x3_adjoint_weights(const bf16_t *w, bf16_t *wf, int cin, int cout, hipStream_t s);
+hipError_t conv3x3_bwd_data(const bf16_t *dz, const bf16_t *wf, float *dx, int n, int h, int w,
+                            int cin, int cout, hipStream_t s);
+// Weight gradient dw[9 cin][cout]; part: conv3x3_dw_splits * 9 cin cout floats.
+int conv3x3_dw_splits(int n, int h, int w, int cin, int cout);
+hipError_t conv3x3_dw(const bf16_t *x, const bf16_t *dz, float *part, float *dw, int n, int h,
+                      int w, int cin, int cout, hipStream_t s);
 hipError_t epilogue(const float *Cp, int splits, size_t mn, int n, const float *bias, int relu,
                     const float *residual, bf16_t *out_bf, float *out_f, hipStream_t s);
 hipError_t relu_bwd(const float *dy, const bf16_t *y, int relu, bf16_t *dz_bf, float *dz_f,
                     size_t total, hipStream_t s);
 // Column sums (cols <= 256); part: scratch of kColsumBlocks * cols floats.
 constexpr int kColsumBlocks = 1024;
+// relu_bwd on [rows][cols] (y null: no ReLU) with db = column sums of dz.
+hipError_t relu_bwd_bias(const float *dy, const bf16_t *y, size_t rows, int cols, bf16_t *dz_bf,
+                         float *db, float *part, hipStream_t s);
 hipError_t colsum(const float *in, size_t rows, int cols, float *out, float *part, hipStream_t s);
 hipError_t pool2(const bf16_t *in, bf16_t *out, int n, int h, int w, int c, hipStream_t s);
 hipError_t pool2_bwd(const float *dout, float *din, int n, int h, int w, int c, int accumulate,

@@ -37,7 +37,7 @@ constexpr uint32_t kMagic[2] = {0x4e4e4c53u, 0x00000001u};  // "SLNN", version 1
 struct Conv {
     int cin, cout, relu, level;
     size_t w, b, gw, gb, mw, vw, mb, vb;  // float32 byte offsets in the parameters
-    size_t w_bf, wt_bf, wf_bf;            // bf16 copies: [9cin][cout], [9cout][cin], [cout][9cin]
+    size_t w_bf, wt_bf, wf_bf;            // bf16 copies: [9cin][cout], adjoint [cin][9cout], [cout][9cin]
     // activations (byte offsets in the workspace; set by the layout)
     size_t x, y, dy, dx;
 };
@@ -47,7 +47,7 @@ struct Acts {
     int n = 0, h = 0, w = 0;
     size_t x_f, x_bf, t_f, gy, y, loss, sum, csum;
     std::vector<size_t> pin, ea, e, cat, da, dd, gdn, ge;
-    size_t dz_bf, dz_f, col, colz, gemm;
+    size_t dz_bf, dw;  // shared by the layers: dZ, and the weight gradient's partial sums
     size_t total = 0;
 };
 
@@ -132,13 +132,6 @@ size_t build_layers(const splotch_nn_config &c, std::vector<Conv> *out) {
     return o;
 }
 
-int gemm_want(size_t P) {
-    size_t want = P / 2048;
-    if (want < 1) want = 1;
-    if (want > 256) want = 256;
-    return (int)want;
-}
-
 // Activation and scratch layout for a batch of n images of h x w.
 Acts layout_acts(splotch_nn *net, int n, int h, int w) {
     const splotch_nn_config &c = net->cfg;
@@ -184,20 +177,15 @@ Acts layout_acts(splotch_nn *net, int n, int h, int w) {
         A.gdn[l] = take(P(l + 1) * c.channels[l + 1] * 4);
     }
     // shared backward scratch: the largest over the layers
-    size_t dz = 0, col = 0, colz = 0, gemm = 0;
+    size_t dz = 0, dw = 0;
     for (const Conv &k : net->conv) {
         const size_t p = P(k.level);
         dz = std::max(dz, p * k.cout);
-        col = std::max(col, p * 9 * k.cin);
-        colz = std::max(colz, p * 9 * k.cout);
-        const int s = gemm_splits((int)std::min<size_t>(p, 0x7FFFFFFF), gemm_want(p));
-        gemm = std::max(gemm, (size_t)s * 9 * k.cin * k.cout);
+        dw = std::max(dw, (size_t)conv3x3_dw_splits(n, h >> k.level, w >> k.level, k.cin, k.cout) *
+                              9 * k.cin * k.cout);
     }
     A.dz_bf = take(dz * 2);
-    A.dz_f = take(dz * 4);
-    A.col = take(col * 2);
-    A.colz = take(colz * 2);
-    A.gemm = take(gemm * 4);
+    A.dw = take(dw * 4);
     // per-layer inputs, outputs and gradients
     for (int l = 0; l < L; ++l) {
         Conv &a = net->conv[enc_a(l)], &b = net->conv[enc_b(l)];
@@ -300,24 +288,15 @@ splotch_status conv_backward(splotch_nn *net, const Conv &k, const Acts &A, void
                              int hh, int ww, const float *dy, bool need_dx, hipStream_t s) {
     const size_t P = (size_t)n * hh * ww;
     bf16_t *dz_bf = W_<bf16_t>(ws, A.dz_bf);
-    float *dz_f = W_<float>(ws, A.dz_f);
-    NN_TRY(relu_bwd(dy, k.relu ? W_<bf16_t>(ws, k.y) : nullptr, k.relu, dz_bf, dz_f, P * k.cout,
-                    s));
-    NN_TRY(colsum(dz_f, P, k.cout, P_<float>(net, k.gb), W_<float>(ws, A.csum), s));
-    bf16_t *col = W_<bf16_t>(ws, A.col);
-    NN_TRY(im2col3x3(W_<bf16_t>(ws, k.x), col, n, hh, ww, k.cin, s));
-    const int want = gemm_want(P);
-    const int splits = gemm_splits((int)P, want);
-    float *cw = W_<float>(ws, A.gemm);
-    NN_TRY(gemm(col, dz_bf, cw, 9 * k.cin, k.cout, (int)P, 9 * k.cin, k.cout, 1, want, s));
-    NN_TRY(epilogue(cw, splits, (size_t)9 * k.cin * k.cout, k.cout, nullptr, 0, nullptr, nullptr,
-                    P_<float>(net, k.gw), s));
+    NN_TRY(relu_bwd_bias(dy, k.relu ? W_<bf16_t>(ws, k.y) : nullptr, P, k.cout, dz_bf,
+                         P_<float>(net, k.gb), W_<float>(ws, A.csum), s));
+    NN_TRY(conv3x3_dw(W_<bf16_t>(ws, k.x), dz_bf, W_<float>(ws, A.dw), P_<float>(net, k.gw), n, hh,
+                      ww, k.cin, k.cout, s));
     if (!need_dx) return SPLOTCH_OK;
-    NN_TRY(flip_weights(P_<bf16_t>(net, k.w_bf), P_<bf16_t>(net, k.wt_bf), k.cout, k.cin, s));
-    bf16_t *colz = W_<bf16_t>(ws, A.colz);
-    NN_TRY(im2col3x3(dz_bf, colz, n, hh, ww, k.cout, s));
-    NN_TRY(gemm(colz, P_<bf16_t>(net, k.wt_bf), W_<float>(ws, k.dx), (int)P, k.cin, 9 * k.cout,
-                9 * k.cout, k.cin, 0, 1, s));
+    NN_TRY(conv3x3_adjoint_weights(P_<bf16_t>(net, k.w_bf), P_<bf16_t>(net, k.wt_bf), k.cin,
+                                   k.cout, s));
+    NN_TRY(conv3x3_bwd_data(dz_bf, P_<bf16_t>(net, k.wt_bf), W_<float>(ws, k.dx), n, hh, ww, k.cin,
+                            k.cout, s));
     return SPLOTCH_OK;
 }
 
