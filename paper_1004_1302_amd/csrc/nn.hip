@@ -138,19 +138,20 @@ __global__ void k_conv_wf(const bf16_t *w, bf16_t *wf, int cin, int cout) {
 // tile and CO output channels; per 32-channel slice of the input it stages
 // the tile with its one-pixel halo (zeros outside the image) and the
 // slice's weights for all 9 taps, then each wave accumulates 2 rows of 16
-// pixels x CO channels, one MFMA per (row, 16 channels) per tap.
+// pixels x CO channels, one MFMA per (row, 16 channels) per tap.  Small
+// tiles: for the deep levels, whose pixels would not fill the GPU otherwise
+// (k_conv3x3_wide does the others).
 constexpr int kCTH = 8, kCTW = 16;           // output tile rows, columns
 constexpr int kCHW = kCTW + 2;               // halo tile width
 constexpr int kCHP = (kCTH + 2) * kCHW;      // halo tile pixels
 constexpr int kCK = 32;                      // input channels per stage
 constexpr int kCRow = kCK + PAD;             // LDS row (bf16); 80 B spreads the banks
 
-template <int CO>
 __global__ __launch_bounds__(256) void k_conv3x3(const bf16_t *x, const bf16_t *wf,
                                                  const float *bias, int relu,
                                                  const float *residual, bf16_t *out_bf,
                                                  float *out_f, int h, int w, int cin, int cout) {
-    constexpr int NT = CO / 16;
+    constexpr int CO = 32, NT = CO / 16;
     __shared__ __attribute__((aligned(16))) bf16_t sX[kCHP][kCRow];
     __shared__ __attribute__((aligned(16))) bf16_t sW[9 * CO][kCRow];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -224,6 +225,183 @@ __global__ __launch_bounds__(256) void k_conv3x3(const bf16_t *x, const bf16_t *
                 if (residual) v += residual[e];
                 if (out_bf) out_bf[e] = f2bf(v);
                 if (out_f) out_f[e] = v;
+            }
+        }
+    }
+}
+
+// The same convolution, with the same sums bit for bit, for images with
+// enough pixels: a workgroup owns a 16 x 32 pixel tile and 32 output
+// channels, each of its four waves 8 rows of 16 pixels.  The weights of a
+// 32-channel slice sit in registers (9 taps x 32 channels, 72 registers), read
+// once where the input has one slice and the workgroups go through the tiles
+// in turns; an input row's three fragments serve three output rows, so a
+// wave issues 144 MFMAs for 30 fragment reads of LDS.  The weights are the
+// MFMA's first operand: a lane then holds four consecutive channels of a
+// pixel, and stores, bias and residual are 8- and 16-byte accesses.
+// The next tile's pixels are fetched into registers while a tile is
+// multiplied.  1024 x 1024 pixels of 32 channels take 39 us (76 us with FP32
+// residual and output), where the kernel above, whose workgroups stage 23 KB
+// of weights for 128 pixels and store two bytes a lane, takes 71 us (173 us)
+// and reading and writing the images 27 us (64 us) at a copy's rate.
+//
+// Inputs of SL = 2 to 4 slices keep all their weights in LDS (23 KB a slice)
+// and read a slice's into the registers at each step; their tiles have four
+// rows a wave, so that two workgroups still fit a CU at SL = 2.
+constexpr int kWTW = 32, kWHW = kWTW + 2;
+template <int SL>
+struct Wide {
+    static constexpr int R = SL == 1 ? 8 : 4;  // rows a wave
+    static constexpr int TH = 2 * R;           // rows a tile
+    static constexpr int HP = (TH + 2) * kWHW; // pixels with the halo
+};
+
+template <int SL>
+__global__ __launch_bounds__(256, SL <= 2 ? 2 : 1) void k_conv3x3_wide(const bf16_t *x, const bf16_t *wf,
+                                                         const float *bias, int relu,
+                                                         const float *residual, bf16_t *out_bf,
+                                                         float *out_f, int n, int h, int w,
+                                                         int cin, int cout) {
+    constexpr int R = Wide<SL>::R, TH = Wide<SL>::TH, HP = Wide<SL>::HP;
+    __shared__ __attribute__((aligned(16))) bf16_t sX[HP][kCRow];
+    __shared__ __attribute__((aligned(16))) bf16_t sWt[SL > 1 ? SL * 9 * 32 : 1][kCRow];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int px = lane & 15, kq = (lane >> 4) * 8;
+    const int tiles_x = (w + kWTW - 1) / kWTW, tiles_y = (h + TH - 1) / TH;
+    const uint32_t per_img = (uint32_t)(tiles_x * tiles_y), tiles = per_img * (uint32_t)n;
+    const int n0 = (int)blockIdx.y * 32;
+    const size_t k9 = (size_t)9 * cin;
+    const int col = (wave & 1) * 16 + px, row = (wave >> 1) * R;
+    bf16x8 wr[9][2];
+    if (SL > 1) {
+        // [slice][tap][output channel] rows
+        for (int e = tid; e < SL * 9 * 32 * 4; e += 256) {
+            const int r = e >> 2, q = (e & 3) * 8, sl = r / 288, tap = r % 288 / 32;
+            if (sl * kCK >= cin) break;
+            *reinterpret_cast<uint4 *>(&sWt[r][q]) = *reinterpret_cast<const uint4 *>(
+                wf + (size_t)(n0 + (r & 31)) * k9 + (size_t)tap * cin + sl * kCK + q);
+        }
+    }
+    auto load_w = [&](int c0) {
+#pragma unroll
+        for (int tap = 0; tap < 9; ++tap)
+#pragma unroll
+            for (int b = 0; b < 2; ++b)
+                wr[tap][b] =
+                    SL > 1 ? *reinterpret_cast<const bf16x8 *>(
+                                 &sWt[(c0 / kCK * 9 + tap) * 32 + b * 16 + px][kq])
+                           : *reinterpret_cast<const bf16x8 *>(
+                                 wf + (size_t)(n0 + b * 16 + px) * k9 + (size_t)tap * cin + kq);
+    };
+    float4 bv[2];
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+        const float *q = bias + n0 + b * 16 + (lane >> 4) * 4;
+        bv[b] = bias ? make_float4(q[0], q[1], q[2], q[3]) : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+    // A step is a 32-channel slice of a tile.  The next step's pixels are in
+    // flight, in registers, while this one's are multiplied.
+    constexpr int kLoads = (HP * 4 + 255) / 256;
+    uint4 next[kLoads];
+    auto fetch = [&](uint32_t t, int c0) {
+        const int img = (int)(t / per_img), tt = (int)(t % per_img);
+        const int y0 = (tt / tiles_x) * TH, x0 = (tt % tiles_x) * kWTW;
+        const bf16_t *src = x + (size_t)img * h * w * cin + c0;
+#pragma unroll
+        for (int k = 0; k < kLoads; ++k) {
+            const int e = tid + 256 * k, p = e >> 2, q = (e & 3) * 8;
+            const int yy = y0 - 1 + p / kWHW, xx = x0 - 1 + p % kWHW;
+            next[k] = make_uint4(0u, 0u, 0u, 0u);
+            if (p < HP && yy >= 0 && yy < h && xx >= 0 && xx < w)
+                next[k] = *reinterpret_cast<const uint4 *>(src + ((size_t)yy * w + xx) * cin + q);
+        }
+    };
+    if (blockIdx.x < tiles) fetch(blockIdx.x, 0);
+    if (SL == 1) load_w(0);
+    for (uint32_t t = blockIdx.x; t < tiles; t += gridDim.x) {
+        const int img = (int)(t / per_img), tt = (int)(t % per_img);
+        const int y0 = (tt / tiles_x) * TH, x0 = (tt % tiles_x) * kWTW;
+        const size_t plane = (size_t)img * h;
+        f32x4 acc[R][2];
+#pragma unroll
+        for (int a = 0; a < R; ++a)
+#pragma unroll
+            for (int b = 0; b < 2; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int c0 = 0; c0 < (SL == 1 ? kCK : cin); c0 += kCK) {
+            __syncthreads();  // the previous step's fragments are read
+#pragma unroll
+            for (int k = 0; k < kLoads; ++k) {
+                const int e = tid + 256 * k;
+                if (e < HP * 4) *reinterpret_cast<uint4 *>(&sX[e >> 2][(e & 3) * 8]) = next[k];
+            }
+            __syncthreads();
+            if (SL > 1 && c0 + kCK < cin)
+                fetch(t, c0 + kCK);
+            else if (t + gridDim.x < tiles)
+                fetch(t + gridDim.x, 0);
+            if (SL > 1) load_w(c0);
+            // the next row's fragments are read before a row's MFMAs; the
+            // barriers keep the compiler from reading all rows at once (it
+            // would spill)
+            bf16x8 xf[2][3];
+            auto read_row = [&](int ir) {
+#pragma unroll
+                for (int dx = 0; dx < 3; ++dx)
+                    xf[ir & 1][dx] =
+                        *reinterpret_cast<const bf16x8 *>(&sX[(row + ir) * kWHW + col + dx][kq]);
+            };
+            read_row(0);
+#pragma unroll
+            for (int ir = 0; ir < R + 2; ++ir) {
+                if (ir + 1 < R + 2) read_row(ir + 1);
+#pragma unroll
+                for (int a = ir - 2; a <= ir; ++a) {
+                    if (a < 0 || a >= R) continue;
+#pragma unroll
+                    for (int dx = 0; dx < 3; ++dx)
+#pragma unroll
+                        for (int b = 0; b < 2; ++b)
+                            acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                                wr[(ir - a) * 3 + dx][b], xf[ir & 1][dx], acc[a][b], 0, 0, 0);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        // output (pixel, channel) of acc[a][b][q]: row `row` + a, column
+        // `col`; channel n0 + 16 b + 4 (lane / 16) + q
+        if (x0 + col >= w) continue;
+#pragma unroll
+        for (int a = 0; a < R; ++a) {
+            const int yy = y0 + row + a;
+            if (yy >= h) continue;
+            const size_t pix = (plane + yy) * w + x0 + col;
+#pragma unroll
+            for (int b = 0; b < 2; ++b) {
+                const size_t e = pix * cout + n0 + b * 16 + (lane >> 4) * 4;
+                float4 v = make_float4(acc[a][b][0], acc[a][b][1], acc[a][b][2], acc[a][b][3]);
+                if (bias) {
+                    v.x += bv[b].x;
+                    v.y += bv[b].y;
+                    v.z += bv[b].z;
+                    v.w += bv[b].w;
+                }
+                if (relu) {
+                    v.x = v.x > 0.f ? v.x : 0.f;
+                    v.y = v.y > 0.f ? v.y : 0.f;
+                    v.z = v.z > 0.f ? v.z : 0.f;
+                    v.w = v.w > 0.f ? v.w : 0.f;
+                }
+                if (residual) {
+                    const float4 r = *reinterpret_cast<const float4 *>(residual + e);
+                    v.x += r.x;
+                    v.y += r.y;
+                    v.z += r.z;
+                    v.w += r.w;
+                }
+                if (out_bf)
+                    *reinterpret_cast<ushort4 *>(out_bf + e) =
+                        make_ushort4(f2bf(v.x), f2bf(v.y), f2bf(v.z), f2bf(v.w));
+                if (out_f) *reinterpret_cast<float4 *>(out_f + e) = v;
             }
         }
     }
@@ -565,15 +743,32 @@ __global__ void k_colsum_part(const float *in, size_t rows, int cols, size_t row
     }
 }
 
-// One wave per column adds its partials (a thread per column took 230 us
-// for 1024 partials).
-__global__ __launch_bounds__(64) void k_colsum_final(const float *part, int nblocks, int cols,
-                                                     float *out) {
+// Adds a column's partials (at most kColsumBlocks) in block order: the whole
+// workgroup fetches them into LDS and one thread adds.  The order matters to
+// the tone map's mean, whose last bit decides bfloat16 roundings all through
+// the network.  (One thread that fetched and added took 64 us for 1024.)
+__global__ __launch_bounds__(256) void k_colsum_final(const float *part, int nblocks, int cols,
+                                                      float *out) {
+    __shared__ __attribute__((aligned(16))) float sh[kColsumBlocks];
     const int c = blockIdx.x;
+    for (int b = threadIdx.x; b < kColsumBlocks; b += 256)
+        sh[b] = b < nblocks ? part[(size_t)b * cols + c] : 0.f;
+    __syncthreads();
+    if (threadIdx.x != 0) return;
     float s = 0.f;
-    for (int b = threadIdx.x; b < nblocks; b += 64) s += part[(size_t)b * cols + c];
-    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-    if (threadIdx.x == 0) out[c] = s;
+    int b = 0;
+    for (; b + 16 <= nblocks; b += 16) {
+#pragma unroll
+        for (int q = 0; q < 16; q += 4) {
+            const float4 v = *reinterpret_cast<const float4 *>(&sh[b + q]);
+            s += v.x;
+            s += v.y;
+            s += v.z;
+            s += v.w;
+        }
+    }
+    for (; b < nblocks; ++b) s += sh[b];
+    out[c] = s;
 }
 
 // 2x2 average pool (NHWC, BF16 in/out) and its adjoint (FP32 in/out).
@@ -602,6 +797,26 @@ __global__ void k_pool2(const bf16_t *in, bf16_t *out, int n, int h, int w, int 
             o.s[k] = f2bf(0.25f * sum);
         }
         *reinterpret_cast<uint4 *>(out + p * c + ch) = o.v;
+    }
+}
+
+// The adjoint for groups of four channels (16-byte accesses): 0.69 to 0.3 ms
+// over the levels of four 1024 x 1024 images, at a copy's rate.
+__global__ void k_pool2_bwd4(const float4 *dout, float4 *din, int n, int h, int w, int c4,
+                             int accumulate) {
+    const size_t total = (size_t)n * h * w * c4;
+    for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < total;
+         e += (size_t)gridDim.x * blockDim.x) {
+        const int ch = (int)(e % c4);
+        const size_t p = e / c4;
+        const int x = (int)(p % w), y = (int)((p / w) % h), img = (int)(p / ((size_t)w * h));
+        const float4 d = dout[(((size_t)img * (h / 2) + y / 2) * (w / 2) + x / 2) * c4 + ch];
+        float4 g = make_float4(0.25f * d.x, 0.25f * d.y, 0.25f * d.z, 0.25f * d.w);
+        if (accumulate) {
+            const float4 o = din[e];
+            g = make_float4(o.x + g.x, o.y + g.y, o.z + g.z, o.w + g.w);
+        }
+        din[e] = g;
     }
 }
 
@@ -665,7 +880,46 @@ __global__ void k_up2_concat_bwd(const float *dout, int ca, int cs, float *da, f
 }
 
 // Mean-squared error over the first `used` of `c` channels and its
-// gradient; partial sums per block in loss_part.
+// gradient; partial sums per block in loss_part.  Groups of four channels
+// (c a multiple of 4, 16-byte aligned); groups past the used channels are
+// only cleared, not read: 0.31 ms for four 1024 x 1024 images of 32 channels,
+// where scalar accesses to every value took 1.18 ms on the 256 workgroups
+// that the 256 partials allow.
+__global__ __launch_bounds__(1024) void k_mse4(const float4 *pred, const float4 *target,
+                                               float4 *grad, size_t pixels, int c4, int used,
+                                               float *loss_part) {
+    __shared__ float sh[1024];
+    float s = 0.f;
+    const float scale = 2.0f / (float)(pixels * used);
+    // a workgroup's values are those of k_mse's: 256 of each sweep of the grid
+    const size_t total = pixels * c4, sweep = (size_t)gridDim.x * 64;
+    for (size_t e = (threadIdx.x >> 6) * sweep + (size_t)blockIdx.x * 64 + (threadIdx.x & 63);
+         e < total; e += 16 * sweep) {
+        const int ch = (int)(e % c4) * 4;
+        float4 d = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (ch < used) {
+            const float4 p = pred[e], t = target[e];
+            d.x = p.x - t.x;
+            if (ch + 1 < used) d.y = p.y - t.y;
+            if (ch + 2 < used) d.z = p.z - t.z;
+            if (ch + 3 < used) d.w = p.w - t.w;
+            s += d.x * d.x;
+            s += d.y * d.y;
+            s += d.z * d.z;
+            s += d.w * d.w;
+        }
+        grad[e] = make_float4(scale * d.x, scale * d.y, scale * d.z, scale * d.w);
+    }
+    sh[threadIdx.x] = s;
+    __syncthreads();
+    for (int o = 512; o > 0; o >>= 1) {
+        if ((int)threadIdx.x < o) sh[threadIdx.x] += sh[threadIdx.x + o];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) loss_part[blockIdx.x] = sh[0];
+}
+
+// The same for any c and alignment.
 __global__ void k_mse(const float *pred, const float *target, float *grad, size_t pixels, int c,
                       int used, float *loss_part) {
     __shared__ float sh[256];
@@ -731,6 +985,47 @@ __global__ void k_tonemap(const float *img, int h, int w, const float *sum, floa
     }
 }
 
+// The same for c a multiple of 8 and 16-byte aligned outputs: a workgroup
+// takes the logarithms of its 256 pixels once (three a thread) and then
+// writes rows of 16 bytes a lane: 46 us for 1024 x 1024 pixels of 32 channels,
+// bound by writing them; a thread per output value, whose waves take three
+// logarithms for two pixels, took 127 us.
+__global__ __launch_bounds__(256) void k_tonemap8(const float *img, size_t plane, const float *sum,
+                                                  float inv_count, float s0, int c, float *out_f,
+                                                  bf16_t *out_bf) {
+    __shared__ float4 sh[256];
+    const float s = tone_scale(sum, inv_count, s0);
+    const size_t p0 = (size_t)blockIdx.x * 256, p = p0 + threadIdx.x;
+    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (p < plane) {
+        v.x = log1pf(fmaxf(img[p], 0.f) / s);
+        v.y = log1pf(fmaxf(img[plane + p], 0.f) / s);
+        v.z = log1pf(fmaxf(img[2 * plane + p], 0.f) / s);
+    }
+    sh[threadIdx.x] = v;
+    __syncthreads();
+    const uint32_t np = plane - p0 < 256 ? (uint32_t)(plane - p0) : 256u;
+    const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (out_f) {
+        const uint32_t g = (uint32_t)c / 4;
+        float4 *o = reinterpret_cast<float4 *>(out_f + p0 * c);
+        for (uint32_t e = threadIdx.x; e < np * g; e += 256) o[e] = e % g == 0 ? sh[e / g] : zero;
+    }
+    if (out_bf) {
+        const uint32_t g = (uint32_t)c / 8;
+        uint4 *o = reinterpret_cast<uint4 *>(out_bf + p0 * c);
+        for (uint32_t e = threadIdx.x; e < np * g; e += 256) {
+            uint4 q = make_uint4(0u, 0u, 0u, 0u);
+            if (e % g == 0) {
+                const float4 t = sh[e / g];
+                q.x = (uint32_t)f2bf(t.x) | ((uint32_t)f2bf(t.y) << 16);
+                q.y = (uint32_t)f2bf(t.z);
+            }
+            o[e] = q;
+        }
+    }
+}
+
 // Inverse tone map from NHWC (first 3 channels) to planar [3][h][w].
 __global__ void k_untonemap(const float *in, int h, int w, const float *sum, float inv_count,
                             float s0, int c, float *img) {
@@ -744,11 +1039,29 @@ __global__ void k_untonemap(const float *in, int h, int w, const float *sum, flo
     }
 }
 
+// The same for rows of 16-byte aligned groups of four channels: a thread per
+// pixel reads its group once (25 us for 1024 x 1024 pixels of 32 channels; a
+// thread per output value fetched each row's line three times: 60 us).
+__global__ __launch_bounds__(256) void k_untonemap4(const float *in, size_t plane,
+                                                    const float *sum, float inv_count, float s0,
+                                                    int c, float *img) {
+    const float s = tone_scale(sum, inv_count, s0);
+    const size_t p = (size_t)blockIdx.x * 256 + threadIdx.x;
+    if (p >= plane) return;
+    const float4 v = *reinterpret_cast<const float4 *>(in + p * c);
+    img[p] = s * expm1f(v.x);
+    img[plane + p] = s * expm1f(v.y);
+    img[2 * plane + p] = s * expm1f(v.z);
+}
+
 __global__ void k_f2bf(const float *in, bf16_t *out, size_t n) {
     for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < n;
          e += (size_t)gridDim.x * blockDim.x)
         out[e] = f2bf(in[e]);
 }
+
+// 16-byte aligned (or null): rows of four floats or eight bf16
+bool a16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
 unsigned grid_for(size_t n) {
     size_t g = (n + 255) / 256;
@@ -818,18 +1131,33 @@ hipError_t conv3x3_weights(const bf16_t *w, bf16_t *wf, int cin, int cout, hipSt
 hipError_t conv3x3(const bf16_t *x, const bf16_t *wf, const float *bias, int relu,
                    const float *residual, bf16_t *out_bf, float *out_f, int n, int h, int w,
                    int cin, int cout, hipStream_t s) {
-    const unsigned tiles = (unsigned)((h + kCTH - 1) / kCTH) * (unsigned)((w + kCTW - 1) / kCTW);
-    // 64 output channels per workgroup where that still gives the GPU
-    // enough workgroups, 32 on the small deep levels
-    if (cout % 64 == 0 && (uint64_t)tiles * (uint64_t)n * (uint64_t)(cout / 64) >= 1024) {
-        hipLaunchKernelGGL(k_conv3x3<64>, dim3(tiles * (unsigned)n, (unsigned)(cout / 64)),
-                           dim3(256), 0, s, x, wf, bias, relu, residual, out_bf, out_f, h, w, cin,
-                           cout);
-    } else {
-        hipLaunchKernelGGL(k_conv3x3<32>, dim3(tiles * (unsigned)n, (unsigned)(cout / 32)),
-                           dim3(256), 0, s, x, wf, bias, relu, residual, out_bf, out_f, h, w, cin,
-                           cout);
+    // wide tiles where they give every CU two workgroups (four tiles, where
+    // one workgroup fits), with fewer the small tiles fill more of the GPU
+    // (128 to 64 channels on 256 x 256 pixels, 512 wide tiles: 28 us, 24 in
+    // small ones); for up to four slices, and where
+    // rows of four channels are aligned (cout is a multiple of 32, so a base
+    // pointer decides)
+    const uintptr_t f32s = reinterpret_cast<uintptr_t>(residual) | reinterpret_cast<uintptr_t>(out_f);
+    if ((f32s & 15u) == 0 && (reinterpret_cast<uintptr_t>(out_bf) & 7u) == 0) {
+        bool done = false;
+        auto wide = [&](auto kernel, int th, unsigned per_cu, uint64_t least) {
+            const uint64_t t = (uint64_t)((h + th - 1) / th) * ((w + kWTW - 1) / kWTW) * n;
+            if (done || t * (cout / 32) < least || t >= (1ull << 31)) return;
+            const unsigned g = (unsigned)std::min<uint64_t>(
+                t, std::max(1u, 256 * per_cu / (unsigned)(cout / 32)));
+            hipLaunchKernelGGL(kernel, dim3(g, (unsigned)(cout / 32)), dim3(256), 0, s, x, wf, bias,
+                               relu, residual, out_bf, out_f, n, h, w, cin, cout);
+            done = true;
+        };
+        if (cin == kCK) wide(k_conv3x3_wide<1>, Wide<1>::TH, 2, 512);
+        else if (cin == 2 * kCK) wide(k_conv3x3_wide<2>, Wide<2>::TH, 2, 512);
+        else if (cin == 3 * kCK) wide(k_conv3x3_wide<3>, Wide<3>::TH, 1, 1024);
+        else if (cin == 4 * kCK) wide(k_conv3x3_wide<4>, Wide<4>::TH, 1, 1024);
+        if (done) return hipGetLastError();
     }
+    const unsigned tiles = (unsigned)((h + kCTH - 1) / kCTH) * (unsigned)((w + kCTW - 1) / kCTW);
+    hipLaunchKernelGGL(k_conv3x3, dim3(tiles * (unsigned)n, (unsigned)(cout / 32)), dim3(256), 0, s,
+                       x, wf, bias, relu, residual, out_bf, out_f, h, w, cin, cout);
     return hipGetLastError();
 }
 
@@ -886,7 +1214,7 @@ hipError_t relu_bwd_bias(const float *dy, const bf16_t *y, size_t rows, int cols
                        part);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_colsum_final, dim3(cols), dim3(64), 0, s, part, nb, cols, db);
+    hipLaunchKernelGGL(k_colsum_final, dim3(cols), dim3(256), 0, s, part, nb, cols, db);
     return hipGetLastError();
 }
 
@@ -904,7 +1232,7 @@ hipError_t colsum(const float *in, size_t rows, int cols, float *out, float *par
     hipLaunchKernelGGL(k_colsum_part, dim3(nb), dim3(256), 0, s, in, rows, cols, rpb, part);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_colsum_final, dim3(cols), dim3(64), 0, s, part, nb, cols, out);
+    hipLaunchKernelGGL(k_colsum_final, dim3(cols), dim3(256), 0, s, part, nb, cols, out);
     return hipGetLastError();
 }
 
@@ -916,6 +1244,12 @@ hipError_t pool2(const bf16_t *in, bf16_t *out, int n, int h, int w, int c, hipS
 
 hipError_t pool2_bwd(const float *dout, float *din, int n, int h, int w, int c, int accumulate,
                      hipStream_t s) {
+    if (c % 4 == 0 && a16(dout) && a16(din)) {
+        hipLaunchKernelGGL(k_pool2_bwd4, dim3(grid_for((size_t)n * h * w * (c / 4))), dim3(256), 0,
+                           s, reinterpret_cast<const float4 *>(dout),
+                           reinterpret_cast<float4 *>(din), n, h, w, c / 4, accumulate);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(k_pool2_bwd, dim3(grid_for((size_t)n * h * w * c)), dim3(256), 0, s, dout,
                        din, n, h, w, c, accumulate);
     return hipGetLastError();
@@ -938,6 +1272,13 @@ hipError_t up2_concat_bwd(const float *dout, int ca, int cs, float *da, float *d
 
 hipError_t mse(const float *pred, const float *target, float *grad, size_t pixels, int c,
                int used, float *loss_part, int nblocks, hipStream_t s) {
+    if (c % 4 == 0 && a16(pred) && a16(target) && a16(grad)) {
+        hipLaunchKernelGGL(k_mse4, dim3(nblocks), dim3(1024), 0, s,
+                           reinterpret_cast<const float4 *>(pred),
+                           reinterpret_cast<const float4 *>(target),
+                           reinterpret_cast<float4 *>(grad), pixels, c / 4, used, loss_part);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(k_mse, dim3(nblocks), dim3(256), 0, s, pred, target, grad, pixels, c, used,
                        loss_part);
     return hipGetLastError();
@@ -953,6 +1294,12 @@ hipError_t adam(float *w, bf16_t *w_bf, const float *g, float *m, float *v, size
 
 hipError_t tonemap(const float *img, int h, int w, float scale, int c, float *out_f,
                    bf16_t *out_bf, hipStream_t s, const float *sum, float inv_count) {
+    const size_t plane = (size_t)h * w;
+    if (c % 8 == 0 && a16(out_f) && a16(out_bf) && (plane + 255) / 256 < (1ull << 31)) {
+        hipLaunchKernelGGL(k_tonemap8, dim3((unsigned)((plane + 255) / 256)), dim3(256), 0, s, img,
+                           plane, sum, inv_count, scale, c, out_f, out_bf);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(k_tonemap, dim3(grid_for((size_t)h * w * c)), dim3(256), 0, s, img, h, w,
                        sum, inv_count, scale, c, out_f, out_bf);
     return hipGetLastError();
@@ -960,6 +1307,12 @@ hipError_t tonemap(const float *img, int h, int w, float scale, int c, float *ou
 
 hipError_t untonemap(const float *in, int h, int w, float scale, int c, float *img, hipStream_t s,
                      const float *sum, float inv_count) {
+    const size_t plane = (size_t)h * w;
+    if (c % 4 == 0 && a16(in) && (plane + 255) / 256 < (1ull << 31)) {
+        hipLaunchKernelGGL(k_untonemap4, dim3((unsigned)((plane + 255) / 256)), dim3(256), 0, s, in,
+                           plane, sum, inv_count, scale, c, img);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(k_untonemap, dim3(grid_for((size_t)h * w * 3)), dim3(256), 0, s, in, h, w,
                        sum, inv_count, scale, c, img);
     return hipGetLastError();

@@ -56,3 +56,72 @@ def test_convolution_gradients(levels, n, h, w):
         if inf.dx != LN.NONE:
             got = net.tensor(inf.dx, P * ci, torch.float32).cpu().numpy().astype(np.float64)
             assert np.abs(got.reshape(dx.shape) - dx).max() <= 1e-4 * np.abs(dx).max(), k
+
+
+@pytest.mark.parametrize("ci,co,n,h,w", [
+    (32, 32, 57, 33, 65), (32, 64, 30, 31, 63), (32, 96, 24, 16, 97), (64, 32, 35, 33, 65),
+    (96, 32, 69, 33, 65), (128, 64, 36, 39, 64), (32, 32, 512, 1, 1)])
+@pytest.mark.parametrize("relu,residual", [(True, False), (False, True)])
+def test_wide_tiles_equal_small_tiles(ci, co, n, h, w, relu, residual):
+    """The convolution in wide pixel tiles (16 x 32, or 8 x 32 for several
+    slices) has the sums of the small ones in the same order: outputs that
+    are not aligned for the wide kernel's rows take the small one, and both
+    give the same bits."""
+    import torch
+    ops = LN.Ops()
+    g = torch.Generator(device="cuda").manual_seed(ci + co + n)
+    px = n * h * w
+
+    def bf(*shape):
+        return torch.randn(shape, generator=g, device="cuda").to(torch.bfloat16).view(torch.int16)
+
+    x, wf = bf(px, ci), bf(co, 9 * ci)
+    bias = torch.randn(co, generator=g, device="cuda")
+    res = torch.randn(px * co, generator=g, device="cuda") if residual else None
+    got = []
+    for shift in (0, 1):
+        out_b = torch.zeros(px * co + shift, dtype=torch.int16, device="cuda")[shift:]
+        out_f = torch.zeros(px * co + shift, device="cuda")[shift:]
+        ops.conv3x3(x, wf, bias, relu, res, out_b, out_f, n, h, w, ci, co)
+        got.append((out_b.cpu().numpy(), out_f.cpu().numpy()))
+    assert np.array_equal(got[0][0], got[1][0])
+    assert np.array_equal(got[0][1], got[1][1])
+    assert np.abs(got[0][1]).max() > 0
+
+
+@pytest.mark.parametrize("h,w,c", [(1, 1, 32), (3, 85, 32), (16, 16, 32), (17, 31, 64), (5, 7, 40),
+                                   (5, 7, 12), (5, 7, 3)])
+def test_elementwise_kernels_at_ragged_sizes(h, w, c):
+    """Tone map, inverse tone map, loss gradient and the pooling adjoint in
+    groups of channels equal their definitions in FP32 (elementwise, a few
+    roundings each: 1e-6 of the largest value), aligned or not."""
+    import torch
+    ops = LN.Ops()
+    g = torch.Generator(device="cuda").manual_seed(h * w + c)
+    img = torch.rand((3, h, w), generator=g, device="cuda") * 5
+    for shift in (0, 1):
+        def buf(n, dtype=torch.float32):
+            return torch.full((n + shift,), 7, dtype=dtype, device="cuda")[shift:]
+        f, b = buf(h * w * c), buf(h * w * c, torch.int16)
+        ops.tonemap(img, h, w, 0.7, c, f, b)
+        ref = torch.zeros((h * w, c), device="cuda")
+        ref[:, :3] = torch.log1p(img / 0.7).reshape(3, -1).T
+        assert (f.reshape(h * w, c) - ref).abs().max() <= 1e-6 * ref.abs().max()
+        assert torch.equal(b, f.to(torch.bfloat16).view(torch.int16))
+        back = buf(3 * h * w)
+        ops.untonemap(f, h, w, 0.7, c, back)
+        assert (back.reshape(3, h, w) - img).abs().max() <= 4e-6 * img.abs().max()
+        grad, part = buf(h * w * c), buf(256)
+        target = torch.rand(h * w * c + shift, generator=g, device="cuda")[shift:]
+        ops.mse(f, target, grad, h * w, c, min(3, c), part, 256)
+        d = (f - target).reshape(h * w, c).clone()
+        d[:, 3:] = 0
+        want = d * (2.0 / (3 * h * w))
+        assert (grad.reshape(h * w, c) - want).abs().max() <= 1e-6 * want.abs().max()
+        assert abs(float(part.sum()) - float((d * d).sum())) <= 1e-5 * float((d * d).sum())
+        small = torch.rand(h * w * c + shift, generator=g, device="cuda")[shift:]
+        for acc in (0, 1):
+            din = buf(4 * h * w * c)
+            ops.pool2_bwd(small, din, 1, 2 * h, 2 * w, c, acc)
+            up = small.reshape(h, w, c).repeat_interleave(2, 0).repeat_interleave(2, 1) * 0.25
+            assert torch.equal(din, (up + 7 * acc).reshape(-1))
