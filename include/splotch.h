@@ -185,7 +185,8 @@ typedef struct splotch_params {
                             composited contributions; other values:
                             SPLOTCH_E_INVALID_ARG */
     int32_t seg_records; /* least records per tile-list segment (one workgroup
-                            each); 0 = 1024.  Long lists are cut into segments
+                            each); 0 = 128 to 1024 (64 px tiles: to 4096) by
+                            the number of pairs.  Long lists are cut into segments
                             whose partial (C, T) are merged front to back:
                             this changes speed and, within rounding, how a
                             tile's sums are associated. */

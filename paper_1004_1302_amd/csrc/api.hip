@@ -20,7 +20,6 @@ namespace {
 
 constexpr uint32_t kMaxChunks = 4096;
 constexpr uint64_t kMaxPairCap = 0xFFFF0000ull;  // pair indices are 32-bit
-constexpr uint32_t kSegMin = 1024;               // least records per list segment
 constexpr int kMaxLanes = 4;                     // batch views in flight at once
 static_assert(kMaxLanes <= kMaxGroup, "a persistent group holds one view per lane");
 
@@ -86,13 +85,14 @@ Layout layout(int64_t n, const splotch_camera *cam, const splotch_params *p, uin
     L.tstart = take((size_t)L.n_tiles * 4);
     L.tend = take((size_t)L.n_tiles * 4);
     L.mcount = take((size_t)L.n_tiles * 16);
-    // segments: seg_len >= max(seg_min, pairs / kSegTarget) keeps the number
-    // of items <= n_tiles + kSegTarget; a tile of L > seg_len records has
+    // segments: seg_len >= pairs / kSegTarget keeps the number of items <=
+    // n_tiles + kSegTarget; a tile of L > seg_len records has
     // ceil(L / seg_len) < 2 L / seg_len segments, so the partial slots of a
-    // pass number < 2 pairs / seg_len <= 2 min(kSegTarget, cap / seg_min)
-    const uint64_t seg_min = p->seg_records > 0 ? (uint64_t)p->seg_records : kSegMin;
+    // pass number < 2 pairs / seg_len
     L.max_items = (uint64_t)L.n_tiles + kSegTarget + 64;
-    L.max_slots = std::min<uint64_t>(2 * kSegTarget, 2 * (cap / seg_min) + 2);
+    L.max_slots = std::min<uint64_t>(
+        2 * kSegTarget,
+        2 * seg_bound(cap, (uint32_t)(L.tile * L.tile), (uint32_t)p->seg_records) + 2);
     L.seg_len = take(4);
     L.flags = take((size_t)SPLOTCH_MAX_VIEWS * 12);  // per view: overflow flag (u32), pairs (u64)
     L.sargs = take(kMaxGroup * sizeof(SplatArgs));    // splat settings of a persistent group
@@ -356,7 +356,7 @@ struct Ctx {
     char *ws;
     hipStream_t s;
     uint64_t split = 0;  // split threshold in pixels, 0 = no splitting
-    uint32_t seg_min = kSegMin;
+    uint32_t seg_min = 0;  // the caller's least records per segment, 0 = by the pairs
     const uint8_t *tile_mask = nullptr;
     Prof prof;
     template <typename T>
@@ -614,7 +614,7 @@ splotch_status prepare(const splotch_particles *P, const splotch_camera *cam,
     if (!fit_capacity(P->n, cam, p, p->workspace_bytes, &c->L)) return SPLOTCH_E_WORKSPACE;
     c->ws = reinterpret_cast<char *>(p->workspace);
     c->s = reinterpret_cast<hipStream_t>(p->stream);
-    c->seg_min = p->seg_records > 0 ? (uint32_t)p->seg_records : kSegMin;
+    c->seg_min = (uint32_t)p->seg_records;
     c->tile_mask = p->tile_mask;
     c->split = split_threshold(p, cam);
     if (c->prof.start(p->profile != 0 && p->stats != nullptr, c->s) != hipSuccess)
@@ -783,9 +783,7 @@ splotch_status enqueue_view(Ctx &c, int32_t v, uint32_t *flags, uint64_t *totals
         if (sa.variant == kSplatRows) {
             // the item count is on the device: a persistent launch over
             // the view's units instead of a grid sized to the most items
-            SplatArgs *dev = c.at<SplatArgs>(c.L.sargs);
-            TRY(store_splat_args(sa, dev, c.s));
-            TRY(launch_splat_multi(dev, 1, sa, c.at<uint32_t>(c.L.unit_next), c.s));
+            TRY(launch_splat_multi(nullptr, 1, sa, c.at<uint32_t>(c.L.unit_next), c.s));
             TRY(launch_merge(sa, c.s));
         } else {
             const uint32_t q = 64;

@@ -232,15 +232,41 @@ struct SplatArgs {
 };
 // How a workgroup walks a tile's list.
 constexpr int kSplatBox = 0, kSplatRows = 1, kSplatLists = 2;
-// Segment length rule (shared by host and device): a multiple of the
-// staging batch nt, at least seg_min, and at least pairs / kSegTarget so
-// that a pass has at most n_tiles + kSegTarget items.
+// Segment length rule (shared by host and device; nt: pixels of a tile): at
+// least pairs / kSegTarget, so that a pass has at most n_tiles + kSegTarget
+// items, and a multiple of nt at least the caller's seg_min.
+// Without one (seg_min = 0) the least length follows the pairs: a list is
+// walked record by record, so where a pass has fewer items than the GPU has
+// room for, its longest list is what it waits for.  A segment then holds
+// 1 / kSegFill(nt) of the pairs (8192 waves of 8x8 blocks, the GPU's 256 CUs
+// hold 6144), from 128 records (below, a segment's setup and its partial image
+// cost what the shorter walk saves) to 1024 (or nt), which was the least for
+// all: the splat of 1e5 particles at 256 x 256 pixels takes 18 us, 74 with it.
 constexpr uint64_t kSegTarget = 65536;
+constexpr uint32_t kSegLow = 128, kSegHigh = 1024;
+__host__ __device__ inline uint64_t seg_fill(uint32_t nt) { return 524288u / nt; }
 __host__ __device__ inline uint32_t seg_len_rule(uint64_t npairs, uint32_t nt, uint32_t seg_min) {
     uint64_t s = (npairs + kSegTarget - 1) / kSegTarget;
-    if (s < seg_min) s = seg_min;
-    s = (s + nt - 1) / nt * nt;
+    if (seg_min) {
+        if (s < seg_min) s = seg_min;
+        s = (s + nt - 1) / nt * nt;
+    } else {
+        uint64_t m = (npairs + seg_fill(nt) - 1) / seg_fill(nt);
+        const uint64_t high = nt > kSegHigh ? nt : kSegHigh;
+        m = m < kSegLow ? kSegLow : (m > high ? high : m);
+        if (s < m) s = m;
+        s = (s + 63) / 64 * 64;
+    }
     return (uint32_t)(s < 0x7FFFFFFFull ? s : 0x7FFFFFFFull);
+}
+// Bound on pairs / seg_len_rule for passes of at most cap pairs: the least
+// lengths give cap / seg_min, or the fill while segments are shorter than
+// kSegHigh (from kSegLow) and cap / kSegHigh beyond.
+inline uint64_t seg_bound(uint64_t cap, uint32_t nt, uint32_t seg_min) {
+    if (seg_min) return cap / seg_min;
+    const uint64_t fill = seg_fill(nt), low = cap / kSegLow;
+    const uint64_t part = low < fill ? low : fill, whole = cap / kSegHigh;
+    return part > whole ? part : whole;
 }
 // Segment bookkeeping for one pass: segment length (from the pair count,
 // host value or device pointer), counts per tile, their scans and the
@@ -259,8 +285,9 @@ hipError_t launch_splat(const SplatArgs &a, uint32_t grid, hipStream_t s);
 // holds the settings that pick the kernel (tile, ordering, compensation,
 // counting, column kernel) and must match every view's.  The views' merge
 // kernels follow separately (launch_merge).
+// With views null, the one view is `like` itself (no member counts).
 // Work is handed out dynamically: next (kUnitCounters uint32, device) holds
-// one unit counter per XCD, cleared by the launcher.
+// one unit counter per XCD, set by the launcher.
 constexpr int kMaxGroup = 4;
 constexpr int kUnitCounters = 8;
 hipError_t store_splat_args(const SplatArgs &a, SplatArgs *dst, hipStream_t s);
