@@ -69,7 +69,7 @@ Layout layout(int64_t n, const splotch_camera *cam, const splotch_params *p, uin
         L.val0 = take(N * 4);
         L.val1 = take(N * 4);
     }
-    L.off = take((N + 1) * 8);
+    L.off = take(std::max((N + 1) * 8, project_partial_words(n) * 4));
     // split particles: a queue part and a count per emission workgroup and
     // the counts' scan (the dense queue reuses cnt, which the pair-offset
     // scan has consumed by then, and the scan's scratch that of that scan)
@@ -396,11 +396,10 @@ splotch_status run_project(const Ctx &c, const splotch_particles *P, const splot
     a.o_bbox = o_bbox;
     a.o_spec = o_spec;
     a.o_key = o_key;
-    TRY(launch_fill_u32(c.at<uint32_t>(c.L.counters), 0u, 2 * kCntN, c.s));
-    uint32_t *range = c.at<uint32_t>(c.L.range);
-    TRY(launch_range_init(range, c.s));
-    a.range_bits = range;
-    TRY(launch_project(a, c.s));
+    a.range_bits = c.at<uint32_t>(c.L.range);
+    // the workgroups' partials where the pair offsets will be
+    a.partial = c.at<uint32_t>(c.L.off);
+    TRY(launch_project(a, 0, nullptr, c.s));
     TRY(const_cast<Prof &>(c.prof).mark(0));
     return SPLOTCH_OK;
 }

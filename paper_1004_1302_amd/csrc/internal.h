@@ -60,12 +60,13 @@ struct ProjectArgs {
     double soh, f;
     int tile, ntx;
     const uint8_t *tile_mask;    // per tile, 0 = skip; null = all tiles
-    uint32_t *range_bits;        // [2*kMaxSpecies] ordered bits of auto min/max (atomics),
-                                 // then [2]: min/max depth key of visible particles
+    uint32_t *range_bits;        // [2*kMaxSpecies] ordered bits of auto min/max, then [2]:
+                                 // min/max depth key of visible particles (none: all ones, 0)
     Rec *rec;
     uint32_t *cnt;   // tile count per particle
     uint32_t *key;   // depth key per particle (kEmptyKey when not visible), may be null
     unsigned long long *counters;  // [kCntN]
+    uint32_t *partial;             // project_partial_words(n): the workgroups' counters and ranges
     // optional stage outputs
     int8_t *o_status;
     int32_t *o_bbox;
@@ -98,11 +99,13 @@ __device__ __forceinline__ uint32_t xcd_contiguous(uint32_t b, uint32_t nblocks)
 // ---- launchers (one per kernel family) ------------------------------------
 hipError_t launch_fill_u32(uint32_t *p, uint32_t v, size_t n, hipStream_t s);
 hipError_t launch_fill_f32(float *p, float v, size_t n, hipStream_t s);
-// Reset the auto-range and depth-key-range slots (min = all ones, max = 0)
-// before the projection.
+// The projection, then the fold of its workgroups' counters and value and
+// depth-key ranges into a.counters and a.range_bits (with keep, into what is
+// there already).  clear (may be null) is set to zero on the way.
 constexpr int kRangeSlots = 2 * kMaxSpecies + 2;
-hipError_t launch_range_init(uint32_t *range_bits, hipStream_t s);
-hipError_t launch_project(const ProjectArgs &a, hipStream_t s);
+constexpr int kProjectWords = kCntN + kRangeSlots;
+size_t project_partial_words(int64_t n);
+hipError_t launch_project(const ProjectArgs &a, int keep, uint32_t *clear, hipStream_t s);
 
 // Exclusive scan of n uint32 counts into n+1 uint64 offsets (out[n] = total).
 size_t scan_u32_u64_scratch_bytes(size_t n);

@@ -158,12 +158,6 @@ __global__ void k_fill_f32(float *p, float v, size_t n) {
     for (size_t k = (size_t)blockIdx.x * blockDim.x + threadIdx.x; k < n; k += stride) p[k] = v;
 }
 
-// Min slots start at all-ones, max slots at zero.
-__global__ void k_init_range(uint32_t *range_bits) {
-    int t = threadIdx.x;
-    if (t < kRangeSlots) range_bits[t] = (t & 1) ? 0u : 0xFFFFFFFFu;
-}
-
 // The projection also finds the exact per-species min/max of valid values
 // for auto ranges (order-free: min and max of binary32 values through their
 // monotone unsigned images); the colour is normalised later, when the splat
@@ -300,15 +294,47 @@ __global__ __launch_bounds__(kThreads) void k_project(ProjectArgs a) {
         }
     }
     __syncthreads();
-    if (threadIdx.x < kCntN && s_cnt[threadIdx.x])
-        atomicAdd(&a.counters[threadIdx.x], (unsigned long long)s_cnt[threadIdx.x]);
-    if (threadIdx.x < a.sp.n && s_lo[threadIdx.x] != 0xFFFFFFFFu) {
-        atomicMin(&a.range_bits[2 * threadIdx.x], s_lo[threadIdx.x]);
-        atomicMax(&a.range_bits[2 * threadIdx.x + 1], s_hi[threadIdx.x]);
-    }
-    if (threadIdx.x == 0 && s_lo[kMaxSpecies] != 0xFFFFFFFFu) {
-        atomicMin(&a.range_bits[2 * kMaxSpecies], s_lo[kMaxSpecies]);
-        atomicMax(&a.range_bits[2 * kMaxSpecies + 1], s_hi[kMaxSpecies]);
+    // this workgroup's partials, word-major (k_project_fold)
+    const int t = threadIdx.x;
+    if (t < kCntN) a.partial[(size_t)t * gridDim.x + blockIdx.x] = s_cnt[t];
+    if (t < 2 * (kMaxSpecies + 1))
+        a.partial[(size_t)(kCntN + t) * gridDim.x + blockIdx.x] = (t & 1) ? s_hi[t >> 1]
+                                                                         : s_lo[t >> 1];
+}
+
+// Folds the workgroups' counters and ranges into the results, or, with
+// `keep`, into what earlier projections left there.  Each wave takes words
+// w, w + 16 of all workgroups, its lanes many at once.  (Each workgroup
+// published them with device-scope atomics on a few words before, which are
+// serialised beyond the XCDs' L2 caches: of the projection of 1e6 particles'
+// 63 us, 50.)  words_clear: counters of the call that start at zero.
+__global__ __launch_bounds__(1024) void k_project_fold(const uint32_t *partial, uint32_t groups,
+                                                       int keep, unsigned long long *counters,
+                                                       uint32_t *range_bits, uint32_t *clear) {
+    const uint32_t lane = threadIdx.x & 63u;
+    if (clear && threadIdx.x == 0) *clear = 0u;
+    for (uint32_t w = threadIdx.x >> 6; w < (uint32_t)kProjectWords; w += 16) {
+        const uint32_t *p = partial + (size_t)w * groups;
+        if (w < (uint32_t)kCntN) {
+            unsigned long long s = 0;
+            for (uint32_t g = lane; g < groups; g += 64) s += p[g];
+            for (int o = 32; o > 0; o >>= 1)
+                s += (unsigned long long)__shfl_xor((long long)s, o, 64);
+            if (lane == 0) counters[w] = keep ? counters[w] + s : s;
+        } else {
+            const uint32_t r = w - kCntN;
+            const bool hi = r & 1u;
+            uint32_t v = hi ? 0u : 0xFFFFFFFFu;
+            for (uint32_t g = lane; g < groups; g += 64) v = hi ? max(v, p[g]) : min(v, p[g]);
+            for (int o = 32; o > 0; o >>= 1) {
+                const uint32_t u = (uint32_t)__shfl_xor((int)v, o, 64);
+                v = hi ? max(v, u) : min(v, u);
+            }
+            if (lane == 0) {
+                if (keep) v = hi ? max(v, range_bits[r]) : min(v, range_bits[r]);
+                range_bits[r] = v;
+            }
+        }
     }
 }
 
@@ -333,22 +359,25 @@ hipError_t launch_fill_f32(float *p, float v, size_t n, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_range_init(uint32_t *range_bits, hipStream_t s) {
-    hipLaunchKernelGGL(k_init_range, dim3(1), dim3(64), 0, s, range_bits);
-    return hipGetLastError();
+static uint32_t project_groups(int64_t n) {
+    // grid-stride, at least 16 particles a thread between 2048 and 16384
+    // workgroups: a 1e9-particle set runs faster on 16384 than on 2048 (13.2
+    // against 15.0 ms)
+    const size_t cap = std::min<size_t>(std::max<size_t>((size_t)n / (16 * kThreads), 2048), 16384);
+    return n > 0 ? grid_for((size_t)n, (unsigned)cap) : 0;
 }
 
-hipError_t launch_project(const ProjectArgs &a, hipStream_t s) {
-    if (a.n == 0) return hipSuccess;
-    // grid-stride, at least 16 particles a thread between 2048 and 16384
-    // workgroups: each workgroup publishes its counters and value ranges
-    // with device-scope atomics on a few words, which are serialised beyond
-    // the XCDs' L2 caches (16384 workgroups took 0.2 ms more than 2048 on a
-    // 1e7-particle set), while a 1e9-particle set runs faster on 16384 than
-    // on 2048 (13.2 against 15.0 ms)
-    const size_t cap = std::min<size_t>(std::max<size_t>((size_t)a.n / (16 * kThreads), 2048), 16384);
-    hipLaunchKernelGGL(k_project, dim3(grid_for((size_t)a.n, (unsigned)cap)), dim3(kThreads), 0, s,
-                       a);
+size_t project_partial_words(int64_t n) { return (size_t)kProjectWords * project_groups(n); }
+
+hipError_t launch_project(const ProjectArgs &a, int keep, uint32_t *clear, hipStream_t s) {
+    const uint32_t groups = project_groups(a.n);
+    if (groups) {
+        hipLaunchKernelGGL(k_project, dim3(groups), dim3(kThreads), 0, s, a);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(k_project_fold, dim3(1), dim3(1024), 0, s, a.partial, groups, keep,
+                       a.counters, a.range_bits, clear);
     return hipGetLastError();
 }
 

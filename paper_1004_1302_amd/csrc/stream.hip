@@ -84,7 +84,8 @@ splotch_particles soa_at(char *base, size_t n, Fields f) {
 }
 
 struct StreamLayout {
-    size_t stage[2], rec, cnt, key, counters, range, flags, pos, scan, hist, slab, slab_n, render;
+    size_t stage[2], rec, cnt, key, counters, range, partial, flags, pos, scan, hist, slab, slab_n,
+        render;
     size_t render_bytes, total;
 };
 
@@ -104,6 +105,7 @@ StreamLayout stream_layout(int64_t subset, int64_t slab, Fields f, size_t render
     L.key = take(S * 4);
     L.counters = take(kCntN * 8);
     L.range = take(kRangeSlots * 4);
+    L.partial = take(project_partial_words(subset) * 4);
     L.flags = take(S * 4);
     L.pos = take(S * 4);
     L.scan = take(scan_u32_scratch_bytes(S));
@@ -316,7 +318,8 @@ splotch_status splotch_render_stream(const splotch_particles *host, int64_t subs
     // projection of one staged subset: record, tile count, depth key
     uint32_t *range = reinterpret_cast<uint32_t *>(ws + L.range);
     unsigned long long *counters = reinterpret_cast<unsigned long long *>(ws + L.counters);
-    auto project = [&](const splotch_particles &D, const splotch_params *pp) -> splotch_status {
+    auto project = [&](const splotch_particles &D, const splotch_params *pp,
+                       int keep) -> splotch_status {
         ProjectArgs a;
         memset(&a, 0, sizeof a);
         a.cam = cam_dev(cam);
@@ -340,7 +343,8 @@ splotch_status splotch_render_stream(const splotch_particles *host, int64_t subs
         a.cnt = reinterpret_cast<uint32_t *>(ws + L.cnt);
         a.key = reinterpret_cast<uint32_t *>(ws + L.key);
         a.counters = counters;
-        S_TRY(launch_project(a, s));
+        a.partial = reinterpret_cast<uint32_t *>(ws + L.partial);
+        S_TRY(launch_project(a, keep, nullptr, s));
         return SPLOTCH_OK;
     };
 
@@ -349,12 +353,17 @@ splotch_status splotch_render_stream(const splotch_particles *host, int64_t subs
     std::vector<uint32_t> h_hist;
     unsigned long long cnt_host[kCntN] = {0, 0, 0, 0};
     if (ordered || any_auto || params->stats) {
-        S_TRY(launch_fill_u32(reinterpret_cast<uint32_t *>(counters), 0u, 2 * kCntN, s));
-        S_TRY(launch_range_init(range, s));
+        if (host->n == 0) {
+            // no subset sets them
+            splotch_particles none;
+            memset(&none, 0, sizeof none);
+            if ((r = project(none, params, 0)) != SPLOTCH_OK) return r;
+        }
         if (ordered) S_TRY(launch_fill_u32(hist, 0u, kBins, s));
         r = for_each_subset(host, subset, ws, L, f, s, cl,
-                            [&](int64_t, const splotch_particles &D) -> splotch_status {
-                                splotch_status q = project(D, params);
+                            [&](int64_t k, const splotch_particles &D) -> splotch_status {
+                                // statistics and ranges of all subsets together
+                                splotch_status q = project(D, params, k > 0);
                                 if (q != SPLOTCH_OK || !ordered) return q;
                                 hipLaunchKernelGGL(k_key_hist, dim3(grid_of((size_t)D.n)),
                                                    dim3(256), 0, s,
@@ -423,7 +432,7 @@ splotch_status splotch_render_stream(const splotch_particles *host, int64_t subs
             r = for_each_subset(
                 host, subset, ws, L, f, s, cl,
                 [&](int64_t, const splotch_particles &D) -> splotch_status {
-                    splotch_status qq = project(D, &rp);
+                    splotch_status qq = project(D, &rp, 0);
                     if (qq != SPLOTCH_OK) return qq;
                     const size_t n = (size_t)D.n;
                     hipLaunchKernelGGL(k_slab_flags, dim3(grid_of(n)), dim3(256), 0, s,
