@@ -26,7 +26,7 @@ static_assert(kMaxLanes <= kMaxGroup, "a persistent group holds one view per lan
 struct Layout {
     size_t rec, cnt, key0, key1, val0, val1, off, scan, radix, counters, range, bounds;
     size_t tstart, tend, mcount, seg_len, nseg, nmulti, seg_off, part_off, seg_scan, item_tile;
-    size_t partial, flags, sargs, unit_next, split, split_cnt, split_off;
+    size_t partial, flags, sargs, unit_next, split, split_cnt, split_off, split_total;
     size_t pk0, pk1, pv0, pv1;
     uint64_t max_items, max_slots;
     size_t total;
@@ -82,6 +82,8 @@ Layout layout(int64_t n, const splotch_camera *cam, const splotch_params *p, uin
     L.counters = take(kCntN * 8);
     L.range = take(kRangeSlots * 4);
     L.bounds = take((2 + 2 * (kMaxChunks + 1)) * 8);
+    // cleared together, in this order, before the tile ranges
+    L.split_total = take(4);
     L.tstart = take((size_t)L.n_tiles * 4);
     L.tend = take((size_t)L.n_tiles * 4);
     L.mcount = take((size_t)L.n_tiles * 16);
@@ -399,7 +401,7 @@ splotch_status run_project(const Ctx &c, const splotch_particles *P, const splot
     a.range_bits = c.at<uint32_t>(c.L.range);
     // the workgroups' partials where the pair offsets will be
     a.partial = c.at<uint32_t>(c.L.off);
-    TRY(launch_project(a, 0, nullptr, c.s));
+    TRY(launch_project(a, 0, c.at<uint32_t>(c.L.split_total), c.s));
     TRY(const_cast<Prof &>(c.prof).mark(0));
     return SPLOTCH_OK;
 }
@@ -492,6 +494,7 @@ splotch_status run_bin_chunk(const Ctx &c, const uint32_t *order, uint32_t idx_m
     e.split_off = c.at<uint64_t>(c.L.split_off);
     e.split_scratch = c.at<void>(c.L.scan);
     e.split_dense = c.at<uint32_t>(c.L.cnt);
+    e.split_total = c.at<uint32_t>(c.L.split_total);
     TRY(launch_emit(e, c.s));
     TRY(const_cast<Prof &>(c.prof).mark(3));
     int bits = 0;
@@ -503,7 +506,8 @@ splotch_status run_bin_chunk(const Ctx &c, const uint32_t *order, uint32_t idx_m
     *vals = in1 ? pv1 : pv0;
     const uint32_t key_mask = e.qshift ? (1u << e.qshift) - 1u : 0xFFFFFFFFu;
     TRY(launch_tile_ranges(keys, (size_t)npairs, nullptr, c.at<uint32_t>(c.L.tstart),
-                           c.at<uint32_t>(c.L.tend), c.L.n_tiles, key_mask, c.s));
+                           c.at<uint32_t>(c.L.tend), c.L.n_tiles, key_mask,
+                           c.at<uint32_t>(c.L.split_total), c.s));
     if (keys_out) *keys_out = keys;
     TRY(const_cast<Prof &>(c.prof).mark(4));
     return SPLOTCH_OK;
@@ -721,6 +725,7 @@ splotch_status enqueue_view(Ctx &c, int32_t v, uint32_t *flags, uint64_t *totals
         e.split_off = c.at<uint64_t>(c.L.split_off);
         e.split_scratch = c.at<void>(c.L.scan);
         e.split_dense = c.at<uint32_t>(c.L.cnt);
+        e.split_total = c.at<uint32_t>(c.L.split_total);
         uint32_t *pk0 = c.at<uint32_t>(c.L.pk0), *pk1 = c.at<uint32_t>(c.L.pk1);
         uint32_t *pv0 = c.at<uint32_t>(c.L.pv0), *pv1 = c.at<uint32_t>(c.L.pv1);
         e.pair_key = pk0;
@@ -737,7 +742,8 @@ splotch_status enqueue_view(Ctx &c, int32_t v, uint32_t *flags, uint64_t *totals
         const uint32_t *vals = in1 ? pv1 : pv0;
         uint32_t *ts = c.at<uint32_t>(c.L.tstart), *te = c.at<uint32_t>(c.L.tend);
         TRY(launch_tile_ranges(keys, (size_t)cap, total, ts, te, Lv.n_tiles,
-                               e.qshift ? (1u << e.qshift) - 1u : 0xFFFFFFFFu, c.s));
+                               e.qshift ? (1u << e.qshift) - 1u : 0xFFFFFFFFu,
+                               c.at<uint32_t>(c.L.split_total), c.s));
         TRY(launch_segments(ts, te, Lv.n_tiles, cap, total, nt, c.seg_min,
                             c.at<uint32_t>(c.L.seg_len), c.at<uint32_t>(c.L.nseg),
                             c.at<uint32_t>(c.L.nmulti), c.at<uint64_t>(c.L.seg_off),
@@ -977,7 +983,9 @@ splotch_status splotch_render(const splotch_particles *P, const splotch_camera *
     sa.qshift = block_mask_shift(c.L.tile, c.L.n_tiles);
     // member statistics only where they are asked for (profile level 2)
     sa.count = (p->stats != nullptr && p->profile >= 2) ? 1 : 0;
-    TRY(launch_fill_u32(c.at<uint32_t>(c.L.mcount), 0u, (size_t)c.L.n_tiles * 4, c.s));
+    // the other strategies always count, and stage timing reads the counts
+    if (sa.count || sa.variant != kSplatRows || c.prof.on)
+        TRY(launch_fill_u32(c.at<uint32_t>(c.L.mcount), 0u, (size_t)c.L.n_tiles * 4, c.s));
 
     const uint64_t total = plan.back();
     if (total == 0) {

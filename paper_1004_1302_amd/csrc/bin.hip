@@ -100,7 +100,7 @@ __global__ __launch_bounds__(kThreads) void k_emit_waves(EmitArgs a) {
     __shared__ uint32_t s_first[kThreads];  // first slot in the wave's run
     __shared__ uint32_t s_off[kThreads];    // first slot, from the wave's first pair
     __shared__ uint32_t s_b0[kThreads], s_b1[kThreads], s_idx[kThreads];
-    __shared__ uint32_t s_nsplit;
+    __shared__ uint32_t s_nsplit, s_split[kThreads], s_place;
     if (threadIdx.x == 0) s_nsplit = 0;
     __syncthreads();
     const uint32_t lane = threadIdx.x & 63u;
@@ -124,15 +124,29 @@ __global__ __launch_bounds__(kThreads) void k_emit_waves(EmitArgs a) {
                 split = bw * bh > a.split_pixels;
             }
             if (split) {
-                const uint32_t q = atomicAdd(&s_nsplit, 1u);
-                a.split_list[(size_t)blockIdx.x * kThreads + q] = (uint32_t)k;
+                s_split[atomicAdd(&s_nsplit, 1u)] = (uint32_t)k;
             } else if (o0 - a.base + c > a.cap && a.overflow) {
                 *a.overflow = 1u;
             }
         }
     }
     __syncthreads();
-    if (threadIdx.x == 0 && a.split_list) a.split_count[blockIdx.x] = s_nsplit;
+    if (a.split_list) {
+        const uint32_t m = s_nsplit;
+        if (a.split_total) {
+            // straight into the dense queue: one atomic a workgroup that has
+            // split particles
+            if (m) {
+                if (threadIdx.x == 0) s_place = atomicAdd(a.split_total, m);
+                __syncthreads();
+                if (threadIdx.x < m) a.split_dense[s_place + threadIdx.x] = s_split[threadIdx.x];
+            }
+        } else {
+            if (threadIdx.x < m)
+                a.split_list[(size_t)blockIdx.x * kThreads + threadIdx.x] = s_split[threadIdx.x];
+            if (threadIdx.x == 0) a.split_count[blockIdx.x] = m;
+        }
+    }
     if (k0 >= a.last) return;  // the whole wave is past the end
     // the wave's run: its particles' slots in order, split ones left out
     // (at most 64 particles of at most (16384 / 8)^2 tiles each)
@@ -191,15 +205,18 @@ __global__ void k_split_compact(EmitArgs a, uint32_t nblocks) {
 }
 
 // Split particles: the waves of the grid take the dense queue's particles
-// in turn, and a wave's lanes write pair t of its particle (its t-th tile,
-// in k_emit's order) at the particle's offset + t.
+// in turn, kSplitParts waves a particle, and their lanes write pair t of it
+// (its t-th tile, in k_emit's order) at the particle's offset + t.  (One wave
+// wrote the 8160 tiles of a screen-sized particle at full HD in 45 us.)
+constexpr uint32_t kSplitParts = 8;
 __global__ __launch_bounds__(kThreads) void k_emit_split(EmitArgs a, uint32_t nblocks) {
     const uint32_t lane = threadIdx.x & 63u;
-    const uint64_t total = a.split_off[nblocks];
+    const uint64_t total = a.split_total ? *a.split_total : a.split_off[nblocks];
     const uint64_t waves = (uint64_t)gridDim.x * (kThreads / 64);
-    for (uint64_t e = (uint64_t)blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6); e < total;
-         e += waves) {
-        const uint64_t k = a.split_dense[e];
+    for (uint64_t u = (uint64_t)blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
+         u < total * kSplitParts; u += waves) {
+        const uint32_t t0 = (uint32_t)(u % kSplitParts) * 64;
+        const uint64_t k = a.split_dense[u / kSplitParts];
         const uint64_t o0 = a.off[k];
         const uint32_t c = (uint32_t)(a.off[k + 1] - o0);
         const uint32_t i = a.order ? (a.order[k] & a.idx_mask) : (uint32_t)k;
@@ -210,7 +227,7 @@ __global__ __launch_bounds__(kThreads) void k_emit_split(EmitArgs a, uint32_t nb
         const int tx0 = i0 / T, ty0 = j0 / T, nx = i1 / T - tx0 + 1;
         const uint64_t o = o0 - a.base;
         if (o + c > a.cap && a.overflow && lane == 0) *a.overflow = 1u;
-        for (uint32_t t = lane; t < c; t += 64) {
+        for (uint32_t t = t0 + lane; t < c; t += 64 * kSplitParts) {
             if (o + t >= a.cap) break;
             const int tx = tx0 + (int)(t % (uint32_t)nx), ty = ty0 + (int)(t / (uint32_t)nx);
             a.pair_key[o + t] = pair_key(a, tx, ty, i0, i1, j0, j1, bb.y);
@@ -314,28 +331,37 @@ hipError_t launch_emit(const EmitArgs &a, hipStream_t s) {
     EmitArgs e = a;
     if (e.tile_mask) e.split_list = nullptr;  // split only where pair t is tile t
     const uint32_t nblocks = (uint32_t)((n + kThreads - 1) / kThreads);
+    // A counter for the whole grid where few workgroups can ask it: device
+    // atomics on one address are serialised (about 5 ns each, 20 us for
+    // 4096), which two launches and their waits cost too; 1e9 particles'
+    // 3.9e6 workgroups go through the counts' scan.
+    if (nblocks > 4096) e.split_total = nullptr;
     if (e.tile_mask)
         hipLaunchKernelGGL(k_emit, dim3(nblocks), dim3(kThreads), 0, s, e);
     else
         hipLaunchKernelGGL(k_emit_waves, dim3(nblocks), dim3(kThreads), 0, s, e);
     hipError_t r = hipGetLastError();
     if (r != hipSuccess || !e.split_list) return r;
-    if ((r = launch_scan_u32_u64(e.split_count, e.split_off, nblocks, e.split_scratch, s)) !=
-        hipSuccess)
-        return r;
-    hipLaunchKernelGGL(k_split_compact, dim3((nblocks + kThreads - 1) / kThreads), dim3(kThreads),
-                       0, s, e, nblocks);
-    if ((r = hipGetLastError()) != hipSuccess) return r;
-    hipLaunchKernelGGL(k_emit_split, dim3(2048), dim3(kThreads), 0, s, e, nblocks);
+    if (!e.split_total) {
+        if ((r = launch_scan_u32_u64(e.split_count, e.split_off, nblocks, e.split_scratch, s)) !=
+            hipSuccess)
+            return r;
+        hipLaunchKernelGGL(k_split_compact, dim3((nblocks + kThreads - 1) / kThreads),
+                           dim3(kThreads), 0, s, e, nblocks);
+        if ((r = hipGetLastError()) != hipSuccess) return r;
+    }
+    // kSplitParts waves per particle of the emission at most
+    const uint32_t groups =
+        (uint32_t)std::min<uint64_t>(2048, (n * kSplitParts + kThreads / 64 - 1) / (kThreads / 64));
+    hipLaunchKernelGGL(k_emit_split, dim3(groups), dim3(kThreads), 0, s, e, nblocks);
     return hipGetLastError();
 }
 
 hipError_t launch_tile_ranges(const uint32_t *sorted_keys, size_t n_pairs,
                               const uint64_t *n_pairs_dev, uint32_t *start, uint32_t *end,
-                              uint32_t n_tiles, uint32_t key_mask, hipStream_t s) {
-    hipError_t e = launch_fill_u32(start, 0u, n_tiles, s);
-    if (e != hipSuccess) return e;
-    e = launch_fill_u32(end, 0u, n_tiles, s);
+                              uint32_t n_tiles, uint32_t key_mask, uint32_t *clear,
+                              hipStream_t s) {
+    hipError_t e = launch_fill_u32(clear, 0u, (size_t)(end + n_tiles - clear), s);
     if (e != hipSuccess || n_pairs == 0) return e;
     // a count on the device (capacity-sized arrays): a capped grid strides
     // over the live pairs

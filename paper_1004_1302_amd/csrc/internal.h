@@ -173,6 +173,9 @@ struct EmitArgs {
     uint64_t *split_off;
     void *split_scratch;
     uint32_t *split_dense;
+    // the dense queue's length (zero before the launch): small emissions
+    // append to it directly
+    uint32_t *split_total;
 };
 constexpr uint32_t kEmitGroup = 256;  // positions per emission workgroup
 hipError_t launch_emit(const EmitArgs &a, hipStream_t s);
@@ -189,10 +192,12 @@ inline int block_mask_shift(int tile, uint32_t n_tiles) {
     return sorted <= qs ? qs : 0;
 }
 // n_pairs_dev (nullable): live pair count on the device, capped at n_pairs.
-// key_mask: the bits of a pair key that hold the tile index.
+// key_mask: the bits of a pair key that hold the tile index.  clear: words
+// from there to the end of `end` are cleared first (start among them).
 hipError_t launch_tile_ranges(const uint32_t *sorted_keys, size_t n_pairs,
                               const uint64_t *n_pairs_dev, uint32_t *start, uint32_t *end,
-                              uint32_t n_tiles, uint32_t key_mask, hipStream_t s);
+                              uint32_t n_tiles, uint32_t key_mask, uint32_t *clear,
+                              hipStream_t s);
 hipError_t launch_chunk_plan(const uint64_t *off, uint64_t n, uint64_t capacity,
                              uint64_t *bounds, uint32_t max_chunks, hipStream_t s);
 

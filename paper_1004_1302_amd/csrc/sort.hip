@@ -158,49 +158,47 @@ __global__ __launch_bounds__(kT) void k_scan_down(L in, TO *out, size_t n, const
     }
 }
 
-// A scan of at most kSmallTiles tiles in one workgroup: the tiles one after
-// another, each as in k_scan_down with the running total as its partial.
+// A scan of at most kSmallScan values in one workgroup, 16384 at a time.
 // One launch instead of three for the short scans (digit histograms and
-// segment counts of small views, where launches dominate).
-constexpr size_t kSmallTiles = 4;
+// pair offsets of small views, where launches dominate).
+constexpr int kST = 1024, kSTile = kST * kIpt;
+constexpr size_t kSmallScan = 4 * kSTile;
 
 template <typename L, typename TO>
-__global__ __launch_bounds__(kT) void k_scan_small(L in, TO *out, size_t n, TO *total_out) {
-    __shared__ TO s[kTile + kTile / 16];
-    __shared__ TO s_w[kW];
+__global__ __launch_bounds__(kST) void k_scan_small(L in, TO *out, size_t n, TO *total_out) {
+    __shared__ TO s[kSTile + kSTile / 16];
+    __shared__ TO s_w[kST / 64];
     TO carry = 0;
-    for (size_t base = 0; base < n; base += kTile) {
+    for (size_t base = 0; base < n; base += kSTile) {
         decltype(in.raw(0)) r[kIpt];
 #pragma unroll
         for (int q = 0; q < kIpt; ++q) {
-            size_t idx = base + (size_t)q * kT + threadIdx.x;
+            size_t idx = base + (size_t)q * kST + threadIdx.x;
             if (idx < n) r[q] = in.raw(idx);
         }
 #pragma unroll
         for (int q = 0; q < kIpt; ++q) {
-            int l = q * kT + threadIdx.x;
+            int l = q * kST + threadIdx.x;
             size_t idx = base + l;
             s[pad(l)] = idx < n ? (TO)in.finish(r[q]) : (TO)0;
         }
         __syncthreads();
-        TO v[kIpt];
         TO sum = 0;
 #pragma unroll
-        for (int i = 0; i < kIpt; ++i) {
-            v[i] = s[pad(threadIdx.x * kIpt + i)];
-            sum += v[i];
-        }
+        for (int i = 0; i < kIpt; ++i) sum += s[pad(threadIdx.x * kIpt + i)];
         TO tot;
-        TO run = carry + block_excl_scan<kW>(sum, s_w, &tot);
+        TO run = carry + block_excl_scan<kST / 64>(sum, s_w, &tot);
 #pragma unroll
         for (int i = 0; i < kIpt; ++i) {
+            // read again: 1024 threads have 128 registers each
+            const TO v = s[pad(threadIdx.x * kIpt + i)];
             s[pad(threadIdx.x * kIpt + i)] = run;
-            run += v[i];
+            run += v;
         }
         __syncthreads();
 #pragma unroll
         for (int q = 0; q < kIpt; ++q) {
-            int l = q * kT + threadIdx.x;
+            int l = q * kST + threadIdx.x;
             size_t idx = base + l;
             if (idx < n) out[idx] = s[pad(l)];
         }
@@ -233,8 +231,8 @@ hipError_t scan_impl(L in, TO *out, size_t n, TO *total_out, void *scratch, hipS
         return hipGetLastError();
     }
     size_t nb = (n + kTile - 1) / kTile;
-    if (nb <= kSmallTiles) {
-        hipLaunchKernelGGL((k_scan_small<L, TO>), dim3(1), dim3(kT), 0, s, in, out, n, total_out);
+    if (n <= kSmallScan) {
+        hipLaunchKernelGGL((k_scan_small<L, TO>), dim3(1), dim3(kST), 0, s, in, out, n, total_out);
         return hipGetLastError();
     }
     TO *partial = reinterpret_cast<TO *>(scratch);
@@ -272,11 +270,12 @@ __device__ __forceinline__ uint32_t tag_value(uint32_t idx, uint32_t count) {
 // live tiles are those the device count fills, and the XCD-contiguous
 // order is taken over them, so every XCD shares the live work; the
 // capacity's other workgroups write zero histogram columns or return.
+template <int IPT>
 struct PassTiles {
     uint32_t live;  // tiles holding elements
     uint32_t all;   // tiles of the capacity (the histogram's columns)
     __device__ PassTiles(size_t n_live, uint32_t nblocks) {
-        const size_t t = (n_live + kTile - 1) / kTile;
+        const size_t t = (n_live + kT * IPT - 1) / (kT * IPT);
         live = t < nblocks ? (uint32_t)t : nblocks;
         all = nblocks;
     }
@@ -316,7 +315,7 @@ constexpr int kHistCopies = 16;
 
 // One workgroup per tile of the capacity.  DB: digit bits (7 or 8): the
 // histogram has 2^DB columns per tile.
-template <int DB>
+template <int DB, int IPT>
 __global__ __launch_bounds__(kT) void k_rs_hist(const uint32_t *keys, size_t n_cap,
                                                 const uint64_t *n_dev, int shift, uint32_t bias,
                                                 uint32_t *hist, uint32_t nblocks, DeviceKeys dk) {
@@ -326,7 +325,7 @@ __global__ __launch_bounds__(kT) void k_rs_hist(const uint32_t *keys, size_t n_c
         if (!dk.resolve(DB, &bias, &passes)) return;
     }
     const size_t n = live_count(n_cap, n_dev);
-    const PassTiles pt(n, nblocks);
+    const PassTiles<IPT> pt(n, nblocks);
     __shared__ uint32_t sh[kHistCopies][ND];
     const int c = threadIdx.x & (kHistCopies - 1);
     // neighbouring tiles' counts share lines of the digit-major histogram
@@ -338,9 +337,9 @@ __global__ __launch_bounds__(kT) void k_rs_hist(const uint32_t *keys, size_t n_c
     }
     for (int d = threadIdx.x; d < kHistCopies * (int)ND; d += kT) (&sh[0][0])[d] = 0;
     __syncthreads();
-    const size_t base = (size_t)t * kTile;
+    const size_t base = (size_t)t * (kT * IPT);
 #pragma unroll
-    for (int q = 0; q < kIpt; ++q) {
+    for (int q = 0; q < IPT; ++q) {
         size_t idx = base + (size_t)q * kT + threadIdx.x;
         if (idx < n) atomicAdd(&sh[c][((keys[idx] - bias) >> shift) & DM], 1u);
     }
@@ -356,15 +355,15 @@ __global__ __launch_bounds__(kT) void k_rs_hist(const uint32_t *keys, size_t n_c
 // Rank the keys of tile t inside the tile (wave ballots find equal digits,
 // lanes in order, waves in order: stable), reorder the tile in LDS and
 // write each digit run contiguously.
-template <int DB>
+template <int DB, int IPT>
 struct ScatterLds {
-    uint32_t k[kTile], v[kTile];
+    uint32_t k[kT * IPT], v[kT * IPT];
     uint32_t wc[kW][1 << DB];
     uint32_t bs[1 << DB], go[1 << DB], sw[kW];
 };
 
-template <int DB>
-__device__ __forceinline__ void scatter_tile(ScatterLds<DB> &L, uint32_t t, size_t n,
+template <int DB, int IPT>
+__device__ __forceinline__ void scatter_tile(ScatterLds<DB, IPT> &L, uint32_t t, size_t n,
                                              const uint32_t *kin, const uint32_t *vin,
                                              uint32_t *kout, uint32_t *vout, int shift,
                                              uint32_t bias, const uint32_t *hist,
@@ -372,14 +371,14 @@ __device__ __forceinline__ void scatter_tile(ScatterLds<DB> &L, uint32_t t, size
                                              const uint32_t *tag) {
     constexpr uint32_t ND = 1u << DB, DM = ND - 1u;
     const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
-    const size_t base = (size_t)t * kTile;
+    const size_t base = (size_t)t * (kT * IPT);
     for (int d = tid; d < kW * (int)ND; d += kT) (&L.wc[0][0])[d] = 0;
     // dg: the key's digit; entries past the live count take digit 255 so
     // that they rank after every live entry of the tile
-    uint32_t k[kIpt], v[kIpt], r[kIpt], dg[kIpt];
+    uint32_t k[IPT], v[IPT], r[IPT], dg[IPT];
 #pragma unroll
-    for (int j = 0; j < kIpt; ++j) {
-        size_t idx = base + (size_t)w * (kIpt * 64) + (size_t)j * 64 + lane;
+    for (int j = 0; j < IPT; ++j) {
+        size_t idx = base + (size_t)w * (IPT * 64) + (size_t)j * 64 + lane;
         if (idx < n) {
             k[j] = kin[idx];
             v[j] = vin ? vin[idx] : (tag ? tag_value((uint32_t)idx, tag[idx]) : (uint32_t)idx);
@@ -393,7 +392,7 @@ __device__ __forceinline__ void scatter_tile(ScatterLds<DB> &L, uint32_t t, size
     __syncthreads();
     const uint64_t lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
 #pragma unroll
-    for (int j = 0; j < kIpt; ++j) {
+    for (int j = 0; j < IPT; ++j) {
         const uint32_t d = dg[j];
         uint64_t m = ~0ull;
 #pragma unroll
@@ -428,7 +427,7 @@ __device__ __forceinline__ void scatter_tile(ScatterLds<DB> &L, uint32_t t, size
     }
     __syncthreads();
 #pragma unroll
-    for (int j = 0; j < kIpt; ++j) {
+    for (int j = 0; j < IPT; ++j) {
         const uint32_t d = dg[j];
         const uint32_t pos = L.bs[d] + L.wc[w][d] + r[j];
         L.k[pos] = k[j];
@@ -436,9 +435,9 @@ __device__ __forceinline__ void scatter_tile(ScatterLds<DB> &L, uint32_t t, size
     }
     __syncthreads();
     const size_t rem = n - base;
-    const int nvalid = rem < (size_t)kTile ? (int)rem : kTile;
+    const int nvalid = rem < (size_t)(kT * IPT) ? (int)rem : kT * IPT;
 #pragma unroll
-    for (int q = 0; q < kIpt; ++q) {
+    for (int q = 0; q < IPT; ++q) {
         int p = q * kT + tid;
         if (p < nvalid) {
             uint32_t key = L.k[p];
@@ -450,7 +449,7 @@ __device__ __forceinline__ void scatter_tile(ScatterLds<DB> &L, uint32_t t, size
     }
 }
 
-template <int DB>
+template <int DB, int IPT>
 __global__ __launch_bounds__(kT) void k_rs_scatter(const uint32_t *kin, const uint32_t *vin,
                                                    uint32_t *kout, uint32_t *vout, size_t n_cap,
                                                    const uint64_t *n_dev, int shift,
@@ -458,7 +457,7 @@ __global__ __launch_bounds__(kT) void k_rs_scatter(const uint32_t *kin, const ui
                                                    uint32_t nblocks, int write_keys,
                                                    const uint32_t *tag, DeviceKeys dk) {
     const size_t n = live_count(n_cap, n_dev);
-    __shared__ ScatterLds<DB> L;
+    __shared__ ScatterLds<DB, IPT> L;
     if (dk.range) {
         int passes;
         if (!dk.resolve(DB, &bias, &passes)) return;
@@ -469,7 +468,7 @@ __global__ __launch_bounds__(kT) void k_rs_scatter(const uint32_t *kin, const ui
     // one workgroup per tile of the capacity; those past the live tiles (a
     // count on the device) return at once.  The runs two neighbouring tiles
     // write for one digit are adjacent in the output.
-    const PassTiles pt(n, nblocks);
+    const PassTiles<IPT> pt(n, nblocks);
     if (blockIdx.x < pt.live)
         scatter_tile(L, pt.tile(blockIdx.x), n, kin, vin, kout, vout, shift, bias, hist, nblocks,
                      write_keys, tag);
@@ -502,8 +501,22 @@ hipError_t launch_scan_u32(uint32_t *data, size_t n, void *scratch, hipStream_t 
                                                     scratch, s);
 }
 
+// Keys per thread of a pass over n keys.  A workgroup ranks its keys one
+// round of 256 after another; while 1024-key tiles still fit the GPU at once
+// (1024 workgroups, four a CU) the shorter chain wins: a pass of 2e4 keys
+// takes 10 us in them and 21 in 4096-key tiles.  From there on the longer
+// digit runs of 4096-key tiles do.
+constexpr size_t kSmallSort = (size_t)1024 * kT * 4;
+constexpr int sort_ipt(size_t n) { return n <= kSmallSort ? 4 : kIpt; }
+size_t sort_tiles(size_t n) {
+    const size_t t = (size_t)kT * sort_ipt(n);
+    return (n + t - 1) / t;
+}
+
 size_t radix_scratch_bytes(size_t n) {
-    size_t nb = (n + kTile - 1) / kTile;
+    // the most tiles of any count up to n: below the step to large tiles,
+    // or at n
+    size_t nb = std::max(sort_tiles(n), sort_tiles(std::min(n, kSmallSort)));
     if (nb == 0) nb = 1;
     size_t hist = align_up(nb * 256 * sizeof(uint32_t), 256);
     return hist + scan_u32_scratch_bytes(nb * 256);
@@ -511,16 +524,16 @@ size_t radix_scratch_bytes(size_t n) {
 
 // One pass: digit histogram per tile, its scan, the scatter.  A count on
 // the device (n_dev) bounds the live tiles; the grid covers the capacity.
-template <int DB>
+template <int DB, int IPT>
 hipError_t radix_pass(const uint32_t *kin, const uint32_t *vin, uint32_t *kout, uint32_t *vout,
                       size_t n, const uint64_t *n_dev, int shift, uint32_t bias, uint32_t *hist,
                       uint32_t nb, int write_keys, const uint32_t *tag, DeviceKeys dk,
                       void *scan_scratch, hipStream_t s) {
-    hipLaunchKernelGGL((k_rs_hist<DB>), dim3(nb), dim3(kT), 0, s, kin, n, n_dev, shift, bias, hist,
+    hipLaunchKernelGGL((k_rs_hist<DB, IPT>), dim3(nb), dim3(kT), 0, s, kin, n, n_dev, shift, bias, hist,
                        nb, dk);
     hipError_t e = launch_scan_u32(hist, (size_t)nb << DB, scan_scratch, s);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_rs_scatter<DB>), dim3(nb), dim3(kT), 0, s, kin, vin, kout, vout, n,
+    hipLaunchKernelGGL((k_rs_scatter<DB, IPT>), dim3(nb), dim3(kT), 0, s, kin, vin, kout, vout, n,
                        n_dev, shift, bias, hist, nb, write_keys, tag, dk);
     return hipGetLastError();
 }
@@ -533,7 +546,8 @@ hipError_t radix_sort_pairs(uint32_t *k0, uint32_t *v0, uint32_t *k1, uint32_t *
     *result_in_1 = false;
     if (n == 0) return hipSuccess;
     if (key_range && (keys_needed || n_dev)) return hipErrorInvalidValue;
-    const uint32_t nb = (uint32_t)((n + kTile - 1) / kTile);
+    const uint32_t nb = (uint32_t)sort_tiles(n);
+    const bool small = sort_ipt(n) == 4;
     uint32_t *hist = reinterpret_cast<uint32_t *>(scratch);
     void *scan_scratch =
         reinterpret_cast<char *>(scratch) + align_up((size_t)nb * 256 * sizeof(uint32_t), 256);
@@ -552,10 +566,10 @@ hipError_t radix_sort_pairs(uint32_t *k0, uint32_t *v0, uint32_t *k1, uint32_t *
         const uint32_t *tag = (p == 0 && vals_identity) ? tag_counts : nullptr;
         const int wk = (!last || keys_needed) ? 1 : 0;
         const DeviceKeys dk{key_range, v0, v1, p};
-        hipError_t e = db == 7 ? radix_pass<7>(kin, vsrc, kout, vout, n, n_dev, shift, bias, hist,
-                                               nb, wk, tag, dk, scan_scratch, s)
-                               : radix_pass<8>(kin, vsrc, kout, vout, n, n_dev, shift, bias, hist,
-                                               nb, wk, tag, dk, scan_scratch, s);
+        const auto pass = small ? (db == 7 ? radix_pass<7, 4> : radix_pass<8, 4>)
+                                : (db == 7 ? radix_pass<7, kIpt> : radix_pass<8, kIpt>);
+        hipError_t e = pass(kin, vsrc, kout, vout, n, n_dev, shift, bias, hist, nb, wk, tag, dk,
+                            scan_scratch, s);
         if (e != hipSuccess) return e;
         src ^= 1;
     }

@@ -35,3 +35,46 @@ def test_segments_by_pairs(n, tile):
         torch.cuda.synchronize()
         for v in views:
             assert torch.equal(v, cut)
+
+
+@pytest.mark.parametrize("width", [728, 736])
+def test_segments_around_one_workgroup(width):
+    """8190 and 8280 tiles: the segment bookkeeping in one workgroup and in
+    four kernels (same bound as above)."""
+    scene = synth.nfw_halos(60_000, seed=5, n_halos=6, grid=16, width=width, height=720)
+    parts, pal = B.scene_to_device(scene)
+    kw = dict(compensated=True, tile=8)
+    one = B.render(parts, scene.camera, pal, scene.species_params, seg_records=1 << 24, **kw)
+    cut = B.render(parts, scene.camera, pal, scene.species_params, **kw)
+    assert float((cut - one).abs().max()) <= 1e-5 * float(one.abs().max())
+
+
+@pytest.mark.parametrize("n", [1023, 1024, 1025, 16_384, 16_385, 65_536, 65_537,
+                               1_048_576, 1_048_577])
+def test_lists_around_sort_and_scan_sizes(n):
+    """Pair lists (integers, bit-exact) where the radix tiles, the
+    one-workgroup scans and the split particles' queue change: 1024-key tiles
+    up to 2^20 keys, scans of up to 65536 values, a queue counter up to 4096
+    emission workgroups."""
+    import torch
+    scene = synth.nfw_halos(n, seed=n, n_halos=9, grid=16, width=320, height=200)
+    parts, _ = B.scene_to_device(scene)
+    tile, ntx = 16, 20
+    for split in (-1, 300):
+        pr = B.project(parts, scene.camera, scene.species_params, tile=tile)
+        ts, te, pp, total = B.bin_pairs(parts, scene.camera, scene.species_params, tile=tile,
+                                        split_pixels=split)
+        torch.cuda.synchronize()
+        vis = np.nonzero(pr["status"].cpu().numpy() == 0)[0]
+        i0, i1, j0, j1 = (pr["bbox"].cpu().numpy()[vis] // tile).T
+        nx, ny = i1 - i0 + 1, j1 - j0 + 1
+        cnt = nx * ny
+        who = np.repeat(np.arange(vis.size), cnt)
+        t = np.arange(cnt.sum()) - np.repeat(np.cumsum(cnt) - cnt, cnt)
+        tiles = (j0[who] + t // nx[who]) * ntx + i0[who] + t % nx[who]
+        key = pr["key"].cpu().numpy().view(np.uint32)[vis][who]
+        order = np.lexsort((vis[who], key, tiles))
+        assert total == cnt.sum()
+        assert np.array_equal(pp.cpu().numpy().view(np.uint32), vis[who][order])
+        have = np.bincount(tiles, minlength=ts.numel())
+        assert np.array_equal((te - ts).cpu().numpy(), have)
