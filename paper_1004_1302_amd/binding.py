@@ -291,9 +291,15 @@ def get_workspace(nbytes: int, device):
     key = str(device)
     t = _ws_cache.get(key)
     if t is None or t.numel() < nbytes:
-        _ws_cache.pop(key, None)
-        t = None  # the old buffer goes before the larger one comes
-        t = torch.empty(max(nbytes, 256), dtype=torch.uint8, device=device)
+        try:
+            t = torch.empty(max(nbytes, 256), dtype=torch.uint8, device=device)
+        except torch.OutOfMemoryError:
+            # no room beside the old buffer: it goes first, when nothing uses it
+            if _ws_cache.pop(key, None) is None:
+                raise
+            t = None
+            torch.cuda.synchronize(device)
+            t = torch.empty(max(nbytes, 256), dtype=torch.uint8, device=device)
         _ws_cache[key] = t
     assert t.data_ptr() % 256 == 0
     return t
