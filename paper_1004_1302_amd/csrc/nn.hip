@@ -119,6 +119,13 @@ __global__ __launch_bounds__(256) void k_gemm(const bf16_t *A, const bf16_t *B, 
         }
 }
 
+// Tone-map scale: the host value, or the device sum times inv_count (the
+// image mean); a non-positive or non-finite scale becomes 1.
+__device__ __forceinline__ float tone_scale(const float *sum, float inv_count, float s) {
+    if (sum) s = sum[0] * inv_count;
+    return (s > 0.f && s < 3.0e38f) ? s : 1.f;
+}
+
 // ------------------------------------------------------- fused 3x3 convolution
 // Forward weights [cout][9 cin] from the GEMM operand [9 cin][cout]: row n
 // holds output channel n's taps (tap-major, then input channel), so a
@@ -256,12 +263,28 @@ struct Wide {
     static constexpr int HP = (TH + 2) * kWHW; // pixels with the halo
 };
 
-template <int SL>
+//
+// HEAD is the last layer of one image's reconstruction: of its 32 channels
+// three are wanted, mapped back into the planar image.  It multiplies for 16
+// channels, takes the residual from the decimated image itself and writes the
+// image, so that neither the FP32 input and output of 32 channels (134 MB each
+// for 1024 x 1024 pixels) nor a pass that maps back touch memory:
+// 40 us, and 18 for the tone map without its FP32 output, instead of 76, 24 and
+// 47 (floor 18 and 17; a third workgroup a CU needs 36 B of scratch a lane and
+// takes as long).
+struct Head {
+    const float *dec;  // planar [3][h][w]
+    const float *sum;  // its sum and 1 / (3 h w): the tone-map scale
+    float inv_count;
+    float *img;        // planar [3][h][w], may be dec
+};
+template <int SL, bool HEAD = false>
 __global__ __launch_bounds__(256, SL <= 2 ? 2 : 1) void k_conv3x3_wide(const bf16_t *x, const bf16_t *wf,
                                                          const float *bias, int relu,
                                                          const float *residual, bf16_t *out_bf,
                                                          float *out_f, int n, int h, int w,
-                                                         int cin, int cout) {
+                                                         int cin, int cout, Head head) {
+    constexpr int NB = HEAD ? 1 : 2;  // 16-channel blocks
     constexpr int R = Wide<SL>::R, TH = Wide<SL>::TH, HP = Wide<SL>::HP;
     __shared__ __attribute__((aligned(16))) bf16_t sX[HP][kCRow];
     __shared__ __attribute__((aligned(16))) bf16_t sWt[SL > 1 ? SL * 9 * 32 : 1][kCRow];
@@ -272,7 +295,7 @@ __global__ __launch_bounds__(256, SL <= 2 ? 2 : 1) void k_conv3x3_wide(const bf1
     const int n0 = (int)blockIdx.y * 32;
     const size_t k9 = (size_t)9 * cin;
     const int col = (wave & 1) * 16 + px, row = (wave >> 1) * R;
-    bf16x8 wr[9][2];
+    bf16x8 wr[9][NB];
     if (SL > 1) {
         // [slice][tap][output channel] rows
         for (int e = tid; e < SL * 9 * 32 * 4; e += 256) {
@@ -286,16 +309,16 @@ __global__ __launch_bounds__(256, SL <= 2 ? 2 : 1) void k_conv3x3_wide(const bf1
 #pragma unroll
         for (int tap = 0; tap < 9; ++tap)
 #pragma unroll
-            for (int b = 0; b < 2; ++b)
+            for (int b = 0; b < NB; ++b)
                 wr[tap][b] =
                     SL > 1 ? *reinterpret_cast<const bf16x8 *>(
                                  &sWt[(c0 / kCK * 9 + tap) * 32 + b * 16 + px][kq])
                            : *reinterpret_cast<const bf16x8 *>(
                                  wf + (size_t)(n0 + b * 16 + px) * k9 + (size_t)tap * cin + kq);
     };
-    float4 bv[2];
+    float4 bv[NB];
 #pragma unroll
-    for (int b = 0; b < 2; ++b) {
+    for (int b = 0; b < NB; ++b) {
         const float *q = bias + n0 + b * 16 + (lane >> 4) * 4;
         bv[b] = bias ? make_float4(q[0], q[1], q[2], q[3]) : make_float4(0.f, 0.f, 0.f, 0.f);
     }
@@ -322,11 +345,11 @@ __global__ __launch_bounds__(256, SL <= 2 ? 2 : 1) void k_conv3x3_wide(const bf1
         const int img = (int)(t / per_img), tt = (int)(t % per_img);
         const int y0 = (tt / tiles_x) * TH, x0 = (tt % tiles_x) * kWTW;
         const size_t plane = (size_t)img * h;
-        f32x4 acc[R][2];
+        f32x4 acc[R][NB];
 #pragma unroll
         for (int a = 0; a < R; ++a)
 #pragma unroll
-            for (int b = 0; b < 2; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int b = 0; b < NB; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
         for (int c0 = 0; c0 < (SL == 1 ? kCK : cin); c0 += kCK) {
             __syncthreads();  // the previous step's fragments are read
 #pragma unroll
@@ -360,12 +383,46 @@ __global__ __launch_bounds__(256, SL <= 2 ? 2 : 1) void k_conv3x3_wide(const bf1
 #pragma unroll
                     for (int dx = 0; dx < 3; ++dx)
 #pragma unroll
-                        for (int b = 0; b < 2; ++b)
+                        for (int b = 0; b < NB; ++b)
                             acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
                                 wr[(ir - a) * 3 + dx][b], xf[ir & 1][dx], acc[a][b], 0, 0, 0);
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
+        }
+        if constexpr (HEAD) {
+            // the three channels of all rows sit in lanes 0 to 15; each
+            // quarter of the wave takes R / 4 of the rows
+            constexpr int Q = R / 4;
+            const int quarter = lane >> 4;
+            float v[Q][3];
+#pragma unroll
+            for (int a = 0; a < R; ++a)
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    const float t = __shfl(acc[a][0][c], px, 64);
+                    if (a < Q || quarter == a / Q) v[a % Q][c] = t;
+                }
+            const float b3[3] = {bias[0], bias[1], bias[2]};
+            const float sc = tone_scale(head.sum, head.inv_count, 1.0f);
+            const size_t image = (size_t)h * w;
+#pragma unroll
+            for (int j = 0; j < Q; ++j) {
+                const int yy = y0 + row + quarter * Q + j;
+                if (yy >= h || x0 + col >= w) continue;
+                const size_t pix = (size_t)yy * w + x0 + col;
+                float d[3];
+#pragma unroll
+                for (int c = 0; c < 3; ++c) d[c] = head.dec[c * image + pix];
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    // rounded before it is added, as from memory
+                    float t = log1pf(fmaxf(d[c], 0.f) / sc);
+                    asm volatile("" : "+v"(t));
+                    head.img[c * image + pix] = sc * expm1f(v[j][c] + b3[c] + t);
+                }
+            }
+            continue;
         }
         // output (pixel, channel) of acc[a][b][q]: row `row` + a, column
         // `col`; channel n0 + 16 b + 4 (lane / 16) + q
@@ -376,7 +433,7 @@ __global__ __launch_bounds__(256, SL <= 2 ? 2 : 1) void k_conv3x3_wide(const bf1
             if (yy >= h) continue;
             const size_t pix = (plane + yy) * w + x0 + col;
 #pragma unroll
-            for (int b = 0; b < 2; ++b) {
+            for (int b = 0; b < NB; ++b) {
                 const size_t e = pix * cout + n0 + b * 16 + (lane >> 4) * 4;
                 float4 v = make_float4(acc[a][b][0], acc[a][b][1], acc[a][b][2], acc[a][b][3]);
                 if (bias) {
@@ -960,13 +1017,6 @@ __global__ void k_adam(float *w, bf16_t *w_bf, const float *g, float *m, float *
     }
 }
 
-// Tone-map scale: the host value, or the device sum times inv_count (the
-// image mean); a non-positive or non-finite scale becomes 1.
-__device__ __forceinline__ float tone_scale(const float *sum, float inv_count, float s) {
-    if (sum) s = sum[0] * inv_count;
-    return (s > 0.f && s < 3.0e38f) ? s : 1.f;
-}
-
 // Tone map of a planar float image [3][h][w] into NHWC with c channels
 // (channels >= 3 zero): out = log1p(img / s), s > 0 per image.
 __global__ void k_tonemap(const float *img, int h, int w, const float *sum, float inv_count,
@@ -1146,7 +1196,7 @@ hipError_t conv3x3(const bf16_t *x, const bf16_t *wf, const float *bias, int rel
             const unsigned g = (unsigned)std::min<uint64_t>(
                 t, std::max(1u, 256 * per_cu / (unsigned)(cout / 32)));
             hipLaunchKernelGGL(kernel, dim3(g, (unsigned)(cout / 32)), dim3(256), 0, s, x, wf, bias,
-                               relu, residual, out_bf, out_f, n, h, w, cin, cout);
+                               relu, residual, out_bf, out_f, n, h, w, cin, cout, Head{});
             done = true;
         };
         if (cin == kCK) wide(k_conv3x3_wide<1>, Wide<1>::TH, 2, 512);
@@ -1158,6 +1208,23 @@ hipError_t conv3x3(const bf16_t *x, const bf16_t *wf, const float *bias, int rel
     const unsigned tiles = (unsigned)((h + kCTH - 1) / kCTH) * (unsigned)((w + kCTW - 1) / kCTW);
     hipLaunchKernelGGL(k_conv3x3, dim3(tiles * (unsigned)n, (unsigned)(cout / 32)), dim3(256), 0, s,
                        x, wf, bias, relu, residual, out_bf, out_f, h, w, cin, cout);
+    return hipGetLastError();
+}
+
+bool conv3x3_head_fits(int h, int w, int cin) {
+    // where conv3x3 takes the wide tiles for one image
+    const uint64_t t = (uint64_t)((h + Wide<1>::TH - 1) / Wide<1>::TH) * ((w + kWTW - 1) / kWTW);
+    return cin == kCK && t >= 512 && t < (1ull << 31);
+}
+
+hipError_t conv3x3_head(const bf16_t *x, const bf16_t *wf, const float *bias, const float *dec,
+                        const float *sum, float inv_count, float *img, int h, int w, int cout,
+                        hipStream_t s) {
+    const unsigned t = (unsigned)((h + Wide<1>::TH - 1) / Wide<1>::TH) *
+                       (unsigned)((w + kWTW - 1) / kWTW);
+    hipLaunchKernelGGL((k_conv3x3_wide<1, true>), dim3(std::min(t, 512u)), dim3(256), 0, s, x, wf,
+                       bias, 0, nullptr, nullptr, nullptr, 1, h, w, kCK, cout,
+                       Head{dec, sum, inv_count, img});
     return hipGetLastError();
 }
 

@@ -300,8 +300,9 @@ splotch_status conv_backward(splotch_nn *net, const Conv &k, const Acts &A, void
     return SPLOTCH_OK;
 }
 
-splotch_status run_forward(splotch_nn *net, const float *x_f, const bf16_t *x_bf, int n, int h,
-                           int w, float *y, void *ws, size_t ws_bytes, hipStream_t s) {
+// All layers but the last.
+splotch_status run_body(splotch_nn *net, const bf16_t *x_bf, int n, int h, int w, void *ws,
+                        size_t ws_bytes, hipStream_t s) {
     if (!valid_shape(net, n, h, w)) return SPLOTCH_E_INVALID_ARG;
     Acts &A = acts(net, n, h, w);
     if (!ws || ws_bytes < A.total) return SPLOTCH_E_WORKSPACE;
@@ -340,6 +341,15 @@ splotch_status run_forward(splotch_nn *net, const float *x_f, const bf16_t *x_bf
             return r;
         d = A.dd[l];
     }
+    return SPLOTCH_OK;
+}
+
+splotch_status run_forward(splotch_nn *net, const float *x_f, const bf16_t *x_bf, int n, int h,
+                           int w, float *y, void *ws, size_t ws_bytes, hipStream_t s) {
+    splotch_status r = run_body(net, x_bf, n, h, w, ws, ws_bytes, s);
+    if (r != SPLOTCH_OK) return r;
+    Acts &A = acts(net, n, h, w);
+    const splotch_nn_config &c = net->cfg;
     float *yo = W_<float>(ws, A.y);
     if ((r = conv_forward(net, net->conv[out_layer(c)], ws, n, h, w, x_f, yo, s)) != SPLOTCH_OK)
         return r;
@@ -397,15 +407,18 @@ splotch_status run_backward(splotch_nn *net, const float *gy, void *ws, size_t w
 // Tone map n planar images into the workspace's NHWC input (scale = the
 // mean of each decimated image, summed on the device) and optionally their
 // targets with the same scales.
+// f32 = false leaves out the network's FP32 input.
 splotch_status tonemap_batch(splotch_nn *net, const Acts &A, void *ws, const float *const *dec,
-                             const float *const *full, int n, int h, int w, hipStream_t s) {
+                             const float *const *full, int n, int h, int w, hipStream_t s,
+                             bool f32 = true) {
     const int CI = net->cfg.in_channels;
     const size_t P = (size_t)h * w;
     const float inv = 1.0f / (float)(3 * P);
     for (int k = 0; k < n; ++k) {
         float *sum = W_<float>(ws, A.sum) + k;
         NN_TRY(colsum(dec[k], 3 * P, 1, sum, W_<float>(ws, A.csum), s));
-        NN_TRY(tonemap(dec[k], h, w, 1.0f, CI, W_<float>(ws, A.x_f) + k * P * CI,
+        NN_TRY(tonemap(dec[k], h, w, 1.0f, CI,
+                       f32 ? W_<float>(ws, A.x_f) + k * P * CI : nullptr,
                        W_<bf16_t>(ws, A.x_bf) + k * P * CI, s, sum, inv));
         if (full)
             NN_TRY(tonemap(full[k], h, w, 1.0f, CI, W_<float>(ws, A.t_f) + k * P * CI, nullptr, s,
@@ -633,8 +646,25 @@ splotch_status splotch_nn_reconstruct(splotch_nn *net, const float *dec_img, int
     Acts &A = acts(net, 1, h, w);
     if (!workspace || workspace_bytes < A.total) return SPLOTCH_E_WORKSPACE;
     const float *dec[1] = {dec_img};
-    splotch_status r = tonemap_batch(net, A, workspace, dec, nullptr, 1, h, w, s);
+    const Conv &last = net->conv[out_layer(net->cfg)];
+    // the last layer straight into the image, unless that would overwrite
+    // pixels of dec_img that it has yet to read
+    const size_t px3 = (size_t)3 * h * w;
+    const uintptr_t di = reinterpret_cast<uintptr_t>(dec_img),
+                    oi = reinterpret_cast<uintptr_t>(out_img);
+    const bool apart = di == oi || di + px3 * 4 <= oi || oi + px3 * 4 <= di;
+    const bool head = apart && conv3x3_head_fits(h, w, last.cin);
+    splotch_status r = tonemap_batch(net, A, workspace, dec, nullptr, 1, h, w, s, !head);
     if (r != SPLOTCH_OK) return r;
+    if (head) {
+        if ((r = run_body(net, W_<bf16_t>(workspace, A.x_bf), 1, h, w, workspace, workspace_bytes,
+                          s)) != SPLOTCH_OK)
+            return r;
+        NN_TRY(conv3x3_head(W_<bf16_t>(workspace, last.x), P_<bf16_t>(net, last.wf_bf),
+                            P_<float>(net, last.b), dec_img, W_<float>(workspace, A.sum),
+                            1.0f / (float)px3, out_img, h, w, last.cout, s));
+        return SPLOTCH_OK;
+    }
     if ((r = run_forward(net, W_<float>(workspace, A.x_f), W_<bf16_t>(workspace, A.x_bf), 1, h, w,
                          nullptr, workspace, workspace_bytes, s)) != SPLOTCH_OK)
         return r;

@@ -125,3 +125,35 @@ def test_elementwise_kernels_at_ragged_sizes(h, w, c):
             ops.pool2_bwd(small, din, 1, 2 * h, 2 * w, c, acc)
             up = small.reshape(h, w, c).repeat_interleave(2, 0).repeat_interleave(2, 1) * 0.25
             assert torch.equal(din, (up + 7 * acc).reshape(-1))
+
+
+@pytest.mark.parametrize("levels,h,w", [((32,), 512, 512), ((32,), 499, 509), ((32,), 16, 16384),
+                                        ((32, 64), 530, 514), ((32,), 16, 16352)])
+def test_reconstruction_from_the_last_layer(levels, h, w):
+    """The last layer that maps back into the image itself (512 pixel tiles
+    and more; the last size has 511) gives the bits of the separate steps,
+    which an output that overlaps the decimated image takes; in place and
+    with pixels that are negative, infinite or NaN too."""
+    import torch
+    net = LN.UNet(seed=5, levels=levels)
+    ws, nb = net.workspace(1, h, w)
+
+    def reconstruct(src, out):
+        assert net.L.splotch_nn_reconstruct(net.h, LN._p(src), h, w, LN._p(out), LN._p(ws), nb,
+                                            LN._s()) == 0
+        return out.cpu().numpy()
+
+    g = torch.Generator(device="cuda").manual_seed(h + w)
+    dec = torch.rand((3, h, w), generator=g, device="cuda") * 3
+    for special in (False, True):
+        if special:
+            dec[0, 5, 7], dec[1, 9, 4], dec[2, 3, 2] = -1.0, float("inf"), float("nan")
+        n = dec.numel()
+        room = torch.empty(n + 64, device="cuda")
+        room[:n] = dec.reshape(-1)
+        want = reconstruct(room, room[64:])
+        same = dec.reshape(-1).clone()
+        for got in (reconstruct(dec, torch.full((n,), 7.0, device="cuda")),
+                    reconstruct(same, same)):
+            assert np.array_equal(got, want, equal_nan=True)
+        assert np.isfinite(want).any()
