@@ -263,7 +263,6 @@ struct Wide {
     static constexpr int HP = (TH + 2) * kWHW; // pixels with the halo
 };
 
-//
 // HEAD is the last layer of one image's reconstruction: of its 32 channels
 // three are wanted, mapped back into the planar image.  It multiplies for 16
 // channels, takes the residual from the decimated image itself and writes the
