@@ -205,18 +205,24 @@ __global__ void k_split_compact(EmitArgs a, uint32_t nblocks) {
 }
 
 // Split particles: the waves of the grid take the dense queue's particles
-// in turn, kSplitParts waves a particle, and their lanes write pair t of it
-// (its t-th tile, in k_emit's order) at the particle's offset + t.  (One wave
-// wrote the 8160 tiles of a screen-sized particle at full HD in 45 us.)
-constexpr uint32_t kSplitParts = 8;
+// in turn, and their lanes write pair t of it (its t-th tile, in k_emit's
+// order) at the particle's offset + t.  While the queue is too short for the
+// waves, up to eight of them share a particle (one wave writes the 8160 tiles of
+// a screen-sized particle at full HD in 45 us); a longer queue has a wave a
+// particle, most of which have few pairs (emission of 16,202,527 NFW particles
+// seen from inside at full HD, split from 64 pixels up: 0.52 ms, 1.56 with eight
+// waves for each; of 2,646,991 from 4096 up: 0.14, 0.16 with one for each).
+constexpr uint32_t kSplitShift = 3;
 __global__ __launch_bounds__(kThreads) void k_emit_split(EmitArgs a, uint32_t nblocks) {
     const uint32_t lane = threadIdx.x & 63u;
     const uint64_t total = a.split_total ? *a.split_total : a.split_off[nblocks];
     const uint64_t waves = (uint64_t)gridDim.x * (kThreads / 64);
+    uint32_t shift = kSplitShift;
+    while (shift && (total << shift) > 4 * waves) --shift;
     for (uint64_t u = (uint64_t)blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
-         u < total * kSplitParts; u += waves) {
-        const uint32_t t0 = (uint32_t)(u % kSplitParts) * 64;
-        const uint64_t k = a.split_dense[u / kSplitParts];
+         u < total << shift; u += waves) {
+        const uint32_t t0 = ((uint32_t)u & ((1u << shift) - 1u)) * 64;
+        const uint64_t k = a.split_dense[u >> shift];
         const uint64_t o0 = a.off[k];
         const uint32_t c = (uint32_t)(a.off[k + 1] - o0);
         const uint32_t i = a.order ? (a.order[k] & a.idx_mask) : (uint32_t)k;
@@ -227,7 +233,7 @@ __global__ __launch_bounds__(kThreads) void k_emit_split(EmitArgs a, uint32_t nb
         const int tx0 = i0 / T, ty0 = j0 / T, nx = i1 / T - tx0 + 1;
         const uint64_t o = o0 - a.base;
         if (o + c > a.cap && a.overflow && lane == 0) *a.overflow = 1u;
-        for (uint32_t t = t0 + lane; t < c; t += 64 * kSplitParts) {
+        for (uint32_t t = t0 + lane; t < c; t += 64u << shift) {
             if (o + t >= a.cap) break;
             const int tx = tx0 + (int)(t % (uint32_t)nx), ty = ty0 + (int)(t / (uint32_t)nx);
             a.pair_key[o + t] = pair_key(a, tx, ty, i0, i1, j0, j1, bb.y);
@@ -350,9 +356,8 @@ hipError_t launch_emit(const EmitArgs &a, hipStream_t s) {
                            dim3(kThreads), 0, s, e, nblocks);
         if ((r = hipGetLastError()) != hipSuccess) return r;
     }
-    // kSplitParts waves per particle of the emission at most
-    const uint32_t groups =
-        (uint32_t)std::min<uint64_t>(2048, (n * kSplitParts + kThreads / 64 - 1) / (kThreads / 64));
+    const uint32_t groups = (uint32_t)std::min<uint64_t>(
+        2048, ((n << kSplitShift) + kThreads / 64 - 1) / (kThreads / 64));
     hipLaunchKernelGGL(k_emit_split, dim3(groups), dim3(kThreads), 0, s, e, nblocks);
     return hipGetLastError();
 }
