@@ -263,14 +263,13 @@ struct Wide {
     static constexpr int HP = (TH + 2) * kWHW; // pixels with the halo
 };
 
-// HEAD is the last layer of one image's reconstruction: of its 32 channels
-// three are wanted, mapped back into the planar image.  It multiplies for 16
-// channels, takes the residual from the decimated image itself and writes the
-// image, so that neither the FP32 input and output of 32 channels (134 MB each
-// for 1024 x 1024 pixels) nor a pass that maps back touch memory:
-// 40 us, and 18 for the tone map without its FP32 output, instead of 76, 24 and
-// 47 (floor 18 and 17; a third workgroup a CU needs 36 B of scratch a lane and
-// takes as long).
+// HEAD is the last layer of one image's reconstruction.  The residual is the
+// tone map of the decimated image in the first three channels and zero in the
+// others, so it comes from that image itself, and the first three channels are
+// mapped back into the planar image where they are computed: beside the
+// layer's FP32 output neither an FP32 input of 32 channels (134 MB for
+// 1024 x 1024 pixels) nor a pass that maps back touches memory: a
+// reconstruction of that size takes 715 us, 764 in separate steps.
 struct Head {
     const float *dec;  // planar [3][h][w]
     const float *sum;  // its sum and 1 / (3 h w): the tone-map scale
@@ -283,7 +282,7 @@ __global__ __launch_bounds__(256, SL <= 2 ? 2 : 1) void k_conv3x3_wide(const bf1
                                                          const float *residual, bf16_t *out_bf,
                                                          float *out_f, int n, int h, int w,
                                                          int cin, int cout, Head head) {
-    constexpr int NB = HEAD ? 1 : 2;  // 16-channel blocks
+    constexpr int NB = 2;  // 16-channel blocks
     constexpr int R = Wide<SL>::R, TH = Wide<SL>::TH, HP = Wide<SL>::HP;
     __shared__ __attribute__((aligned(16))) bf16_t sX[HP][kCRow];
     __shared__ __attribute__((aligned(16))) bf16_t sWt[SL > 1 ? SL * 9 * 32 : 1][kCRow];
@@ -389,47 +388,43 @@ __global__ __launch_bounds__(256, SL <= 2 ? 2 : 1) void k_conv3x3_wide(const bf1
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
-        if constexpr (HEAD) {
-            // the three channels of all rows sit in lanes 0 to 15; each
-            // quarter of the wave takes R / 4 of the rows
-            constexpr int Q = R / 4;
-            const int quarter = lane >> 4;
-            float v[Q][3];
-#pragma unroll
-            for (int a = 0; a < R; ++a)
-#pragma unroll
-                for (int c = 0; c < 3; ++c) {
-                    const float t = __shfl(acc[a][0][c], px, 64);
-                    if (a < Q || quarter == a / Q) v[a % Q][c] = t;
-                }
-            const float b3[3] = {bias[0], bias[1], bias[2]};
-            const float sc = tone_scale(head.sum, head.inv_count, 1.0f);
-            const size_t image = (size_t)h * w;
+        // output (pixel, channel) of acc[a][b][q]: row `row` + a, column
+        // `col`; channel n0 + 16 b + 4 (lane / 16) + q
+        // HEAD: the image's three channels of all rows sit in lanes 0 to 15;
+        // each quarter of the wave takes the logarithms (and, below, the
+        // exponentials) of R / 4 of the rows.
+        constexpr int Q = R / 4;
+        const bool image = HEAD && n0 == 0;
+        const int quarter = lane >> 4;
+        const size_t plane3 = (size_t)h * w;
+        float tone[HEAD ? Q : 1][3], sc = 1.f;
+        if (image) {
+            sc = tone_scale(head.sum, head.inv_count, 1.0f);
 #pragma unroll
             for (int j = 0; j < Q; ++j) {
                 const int yy = y0 + row + quarter * Q + j;
-                if (yy >= h || x0 + col >= w) continue;
-                const size_t pix = (size_t)yy * w + x0 + col;
-                float d[3];
-#pragma unroll
-                for (int c = 0; c < 3; ++c) d[c] = head.dec[c * image + pix];
+                const bool in = yy < h && x0 + col < w;
 #pragma unroll
                 for (int c = 0; c < 3; ++c) {
+                    const float d = in ? head.dec[c * plane3 + (size_t)yy * w + x0 + col] : 0.f;
+                    tone[j][c] = log1pf(fmaxf(d, 0.f) / sc);
                     // rounded before it is added, as from memory
-                    float t = log1pf(fmaxf(d[c], 0.f) / sc);
-                    asm volatile("" : "+v"(t));
-                    head.img[c * image + pix] = sc * expm1f(v[j][c] + b3[c] + t);
+                    asm volatile("" : "+v"(tone[j][c]));
                 }
             }
-            continue;
         }
-        // output (pixel, channel) of acc[a][b][q]: row `row` + a, column
-        // `col`; channel n0 + 16 b + 4 (lane / 16) + q
-        if (x0 + col >= w) continue;
 #pragma unroll
         for (int a = 0; a < R; ++a) {
             const int yy = y0 + row + a;
-            if (yy >= h) continue;
+            float4 r0 = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (image) {
+                const int from = a / Q * 16 + px;
+                const float t0 = __shfl(tone[a % Q][0], from, 64);
+                const float t1 = __shfl(tone[a % Q][1], from, 64);
+                const float t2 = __shfl(tone[a % Q][2], from, 64);
+                if (lane < 16) r0 = make_float4(t0, t1, t2, 0.f);
+            }
+            if (yy >= h || x0 + col >= w) continue;
             const size_t pix = (plane + yy) * w + x0 + col;
 #pragma unroll
             for (int b = 0; b < NB; ++b) {
@@ -447,8 +442,9 @@ __global__ __launch_bounds__(256, SL <= 2 ? 2 : 1) void k_conv3x3_wide(const bf1
                     v.z = v.z > 0.f ? v.z : 0.f;
                     v.w = v.w > 0.f ? v.w : 0.f;
                 }
-                if (residual) {
-                    const float4 r = *reinterpret_cast<const float4 *>(residual + e);
+                if (HEAD || residual) {
+                    float4 r = b == 0 ? r0 : make_float4(0.f, 0.f, 0.f, 0.f);
+                    if (!HEAD) r = *reinterpret_cast<const float4 *>(residual + e);
                     v.x += r.x;
                     v.y += r.y;
                     v.z += r.z;
@@ -458,6 +454,25 @@ __global__ __launch_bounds__(256, SL <= 2 ? 2 : 1) void k_conv3x3_wide(const bf1
                     *reinterpret_cast<ushort4 *>(out_bf + e) =
                         make_ushort4(f2bf(v.x), f2bf(v.y), f2bf(v.z), f2bf(v.w));
                 if (out_f) *reinterpret_cast<float4 *>(out_f + e) = v;
+            }
+        }
+        if (image) {
+#pragma unroll
+            for (int j = 0; j < Q; ++j) {
+                const int yy = y0 + row + quarter * Q + j;
+                float v[3];
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) {
+                        const float t = __shfl(acc[k * Q + j][0][c], px, 64);
+                        if (k == 0 || quarter == k) v[c] = t;
+                    }
+                if (yy >= h || x0 + col >= w) continue;
+#pragma unroll
+                for (int c = 0; c < 3; ++c)
+                    head.img[c * plane3 + (size_t)yy * w + x0 + col] =
+                        sc * expm1f(v[c] + bias[c] + tone[j][c]);
             }
         }
     }
@@ -1217,12 +1232,13 @@ bool conv3x3_head_fits(int h, int w, int cin) {
 }
 
 hipError_t conv3x3_head(const bf16_t *x, const bf16_t *wf, const float *bias, const float *dec,
-                        const float *sum, float inv_count, float *img, int h, int w, int cout,
-                        hipStream_t s) {
+                        const float *sum, float inv_count, float *y, float *img, int h, int w,
+                        int cout, hipStream_t s) {
     const unsigned t = (unsigned)((h + Wide<1>::TH - 1) / Wide<1>::TH) *
                        (unsigned)((w + kWTW - 1) / kWTW);
-    hipLaunchKernelGGL((k_conv3x3_wide<1, true>), dim3(std::min(t, 512u)), dim3(256), 0, s, x, wf,
-                       bias, 0, nullptr, nullptr, nullptr, 1, h, w, kCK, cout,
+    const unsigned cb = (unsigned)(cout / 32);
+    hipLaunchKernelGGL((k_conv3x3_wide<1, true>), dim3(std::min(t, std::max(1u, 512 / cb)), cb),
+                       dim3(256), 0, s, x, wf, bias, 0, nullptr, nullptr, y, 1, h, w, kCK, cout,
                        Head{dec, sum, inv_count, img});
     return hipGetLastError();
 }

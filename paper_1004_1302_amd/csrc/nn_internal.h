@@ -21,14 +21,15 @@ hipError_t conv3x3_weights(const bf16_t *w, bf16_t *wf, int cin, int cout, hipSt
 hipError_t conv3x3(const bf16_t *x, const bf16_t *wf, const float *bias, int relu,
                    const float *residual, bf16_t *out_bf, float *out_f, int n, int h, int w,
                    int cin, int cout, hipStream_t s);
-// The last layer of one image's reconstruction: img = s expm1(conv3x3(x) +
-// bias + log1p(dec / s)) of the first three channels, planar, with s = sum[0] *
-// inv_count as in tonemap.  Where conv3x3_head_fits; img may be dec, but not
-// overlap it otherwise.
+// The last layer of one image's reconstruction: y = conv3x3(x) + bias + r,
+// [h][w][cout] (16-byte aligned), where r is the tone map log1p(dec / s) in the
+// first three channels and zero in the others, and img = s expm1(y) of those
+// three, planar, with s = sum[0] * inv_count as in tonemap.  Where
+// conv3x3_head_fits; img may be dec, but not overlap it otherwise.
 bool conv3x3_head_fits(int h, int w, int cin);
 hipError_t conv3x3_head(const bf16_t *x, const bf16_t *wf, const float *bias, const float *dec,
-                        const float *sum, float inv_count, float *img, int h, int w, int cout,
-                        hipStream_t s);
+                        const float *sum, float inv_count, float *y, float *img, int h, int w,
+                        int cout, hipStream_t s);
 // Backward-data of the convolution (cin -> cout): dx = conv3x3(dz, adjoint
 // weights), its reduction in (tap, output channel) order.  wf from
 // conv3x3_adjoint_weights (w: the [9 cin][cout] operand).

@@ -653,7 +653,9 @@ splotch_status splotch_nn_reconstruct(splotch_nn *net, const float *dec_img, int
     const uintptr_t di = reinterpret_cast<uintptr_t>(dec_img),
                     oi = reinterpret_cast<uintptr_t>(out_img);
     const bool apart = di == oi || di + px3 * 4 <= oi || oi + px3 * 4 <= di;
-    const bool head = apart && conv3x3_head_fits(h, w, last.cin);
+    float *y = W_<float>(workspace, A.y);
+    const bool head = apart && (reinterpret_cast<uintptr_t>(y) & 15u) == 0 &&
+                      conv3x3_head_fits(h, w, last.cin);
     splotch_status r = tonemap_batch(net, A, workspace, dec, nullptr, 1, h, w, s, !head);
     if (r != SPLOTCH_OK) return r;
     if (head) {
@@ -662,7 +664,7 @@ splotch_status splotch_nn_reconstruct(splotch_nn *net, const float *dec_img, int
             return r;
         NN_TRY(conv3x3_head(W_<bf16_t>(workspace, last.x), P_<bf16_t>(net, last.wf_bf),
                             P_<float>(net, last.b), dec_img, W_<float>(workspace, A.sum),
-                            1.0f / (float)px3, out_img, h, w, last.cout, s));
+                            1.0f / (float)px3, y, out_img, h, w, last.cout, s));
         return SPLOTCH_OK;
     }
     if ((r = run_forward(net, W_<float>(workspace, A.x_f), W_<bf16_t>(workspace, A.x_bf), 1, h, w,
