@@ -250,15 +250,13 @@ SpeciesDev species_dev(const splotch_params *p) {
     return s;
 }
 
+bool valid_colourmap(const splotch_colourmap *m) {
+    return m && m->n_entries >= 2 && m->rgb && (!m->rgb_absorb || m->n_entries_absorb >= 2);
+}
+
 }  // namespace splotch
 
 namespace {
-
-splotch_status validate_colourmap(const splotch_colourmap *m) {
-    if (!m || m->n_entries < 2 || !m->rgb) return SPLOTCH_E_INVALID_ARG;
-    if (m->rgb_absorb && m->n_entries_absorb < 2) return SPLOTCH_E_INVALID_ARG;
-    return SPLOTCH_OK;
-}
 
 // Colour and column settings of the splat (shared by single and batched
 // renders).
@@ -942,7 +940,7 @@ splotch_status splotch_render(const splotch_particles *P, const splotch_camera *
     Ctx c;
     splotch_status st = prepare(P, cam, p, &c);
     if (st != SPLOTCH_OK) return st;
-    if ((st = validate_colourmap(cmap)) != SPLOTCH_OK) return st;
+    if (!valid_colourmap(cmap)) return SPLOTCH_E_INVALID_ARG;
     if (!img || !img->rgb || img->width != cam->width || img->height != cam->height)
         return SPLOTCH_E_INVALID_ARG;
     const int64_t n = P->n;
@@ -1089,7 +1087,7 @@ splotch_status splotch_render_batch(const splotch_particles *P, int32_t n_views,
             big = v;
         }
     }
-    if ((st = validate_colourmap(cmap)) != SPLOTCH_OK) return st;
+    if (!valid_colourmap(cmap)) return SPLOTCH_E_INVALID_ARG;
     if (p->batch_streams < 0 || p->batch_streams > kMaxLanes) return SPLOTCH_E_INVALID_ARG;
     const int K = std::max(1, std::min<int>(p->batch_streams, n_views));
     Ctx c;

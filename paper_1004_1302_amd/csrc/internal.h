@@ -78,6 +78,7 @@ struct ProjectArgs {
 
 struct splotch_camera;
 struct splotch_params;
+struct splotch_colourmap;
 
 namespace splotch {
 
@@ -85,6 +86,7 @@ namespace splotch {
 // settings (api.hip).
 CamDev cam_dev(const splotch_camera *c);
 SpeciesDev species_dev(const splotch_params *p);
+bool valid_colourmap(const splotch_colourmap *m);
 
 // Workgroups are dealt to the 8 XCDs round-robin.  This maps workgroup b
 // of nblocks to the chunk it processes so that each XCD gets a contiguous

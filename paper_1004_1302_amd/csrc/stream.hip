@@ -255,7 +255,9 @@ struct LaneLease {
 };
 
 // The subsets of one call's host set on their way through the two staging
-// buffers.
+// buffers.  A call that ends before its last subset is worked on (an error)
+// waits for the copies it has started: the host set and the workspace are the
+// caller's again when it returns.
 struct Subsets {
     const splotch_particles *H;
     int64_t subset;
@@ -265,7 +267,12 @@ struct Subsets {
     hipStream_t s;
     CopyLane *cl;
     bool ahead = false;  // subset 0 of the next pass is on its way
+    bool whole = false;  // every copy has been waited for on the caller's stream
 
+    ~Subsets() {
+        if (!whole)
+            for (int c = 0; c < kCopyStreams; ++c) (void)hipStreamSynchronize(cl->s[c]);
+    }
     int64_t count() const { return (H->n + subset - 1) / subset; }
     size_t size(int64_t k) const {
         return (size_t)std::min<int64_t>(subset, H->n - k * subset);
@@ -295,16 +302,11 @@ struct Subsets {
         for (int c = 0; c < kCopyStreams; ++c) S_TRY(hipEventRecord(cl->copied[b][c], cl->s[c]));
         return SPLOTCH_OK;
     }
-    // Starts the next pass's first copies.  Only where that pass is certain to
-    // run (it waits for them) or the call ends in quiet().
+    // Starts the copies of the next pass's first subset.
     splotch_status fetch_ahead() {
         if (count() == 0 || ahead) return SPLOTCH_OK;
         ahead = true;
         return issue(0);
-    }
-    // Waits until no copy reads the host set any more.
-    void quiet() {
-        for (int c = 0; c < kCopyStreams; ++c) (void)hipStreamSynchronize(cl->s[c]);
     }
     // Calls work(k, device view) for every subset on the caller's stream.
     template <typename Work>
@@ -364,6 +366,7 @@ splotch_status splotch_render_stream(const splotch_particles *host, int64_t subs
         (reinterpret_cast<uintptr_t>(params->workspace) & 255u))
         return SPLOTCH_E_WORKSPACE;
     if (image->width != cam->width || image->height != cam->height) return SPLOTCH_E_INVALID_ARG;
+    if (!valid_colourmap(cmap)) return SPLOTCH_E_INVALID_ARG;  // before the first copy
     const Fields f = fields_of(host);
     size_t rb = 0;
     if ((r = splotch_workspace_size(std::max(subset, slab), cam, params, 0, &rb)) != SPLOTCH_OK)
@@ -373,7 +376,7 @@ splotch_status splotch_render_stream(const splotch_particles *host, int64_t subs
     hipStream_t s = reinterpret_cast<hipStream_t>(params->stream);
     LaneLease lease;
     if ((r = lease.take()) != SPLOTCH_OK) return r;
-    Subsets subsets{host, subset, ws, L, f, s, &lease.lane};
+    Subsets subsets{host, subset, ws, L, f, s, &lease.lane};  // ends before the lease
     if ((r = subsets.begin()) != SPLOTCH_OK) return r;
     bool ordered = false, any_auto = false;
     for (int q = 0; q < params->n_species; ++q) {
@@ -547,12 +550,10 @@ splotch_status splotch_render_stream(const splotch_particles *host, int64_t subs
                 });
             if (r == SPLOTCH_OK && q > 0) r = subsets.fetch_ahead();
             if (r == SPLOTCH_OK) r = render_set(S);
-            if (r != SPLOTCH_OK) {
-                subsets.quiet();
-                return r;
-            }
+            if (r != SPLOTCH_OK) return r;
         }
     }
+    subsets.whole = true;
     if (n_renders == 0) {
         // nothing visible: the image is still written (cleared or kept)
         splotch_particles E;
