@@ -28,6 +28,7 @@ struct Layout {
     size_t tstart, tend, mcount, seg_len, nseg, nmulti, seg_off, part_off, seg_scan, item_tile;
     size_t partial, flags, sargs, unit_next, split, split_cnt, split_off, split_total;
     size_t pk0, pk1, pv0, pv1;
+    size_t off_bytes, radix_bytes;  // from off and radix on, for the sorts
     uint64_t max_items, max_slots;
     size_t total;
     uint64_t pair_cap;
@@ -69,7 +70,9 @@ Layout layout(int64_t n, const splotch_camera *cam, const splotch_params *p, uin
         L.val0 = take(N * 4);
         L.val1 = take(N * 4);
     }
+    // the projection's partial words (88 bytes for 256 particles) come first
     L.off = take(std::max((N + 1) * 8, project_partial_words(n) * 4));
+    L.off_bytes = o - L.off;
     // split particles: a queue part and a count per emission workgroup and
     // the counts' scan (the dense queue reuses cnt, which the pair-offset
     // scan has consumed by then, and the scan's scratch that of that scan)
@@ -78,12 +81,13 @@ Layout layout(int64_t n, const splotch_camera *cam, const splotch_params *p, uin
     L.split_cnt = take(emit_groups * 4);
     L.split_off = take((emit_groups + 1) * 8);
     L.scan = take(scan_u32_u64_scratch_bytes(N));
-    L.radix = take(radix_scratch_bytes(std::max<size_t>(L.ordered ? N : 0, (size_t)cap)));
     L.counters = take(kCntN * 8);
     L.range = take(kRangeSlots * 4);
-    L.bounds = take((2 + 2 * (kMaxChunks + 1)) * 8);
-    // cleared together, in this order, before the tile ranges
-    L.split_total = take(4);
+    // split_total, in the bounds' last 256 bytes, and the tile ranges are
+    // cleared together, in this order
+    const size_t bounds = (2 + 2 * (kMaxChunks + 1)) * 8;
+    L.bounds = take(bounds + 4);
+    L.split_total = L.bounds + bounds;
     L.tstart = take((size_t)L.n_tiles * 4);
     L.tend = take((size_t)L.n_tiles * 4);
     L.mcount = take((size_t)L.n_tiles * 16);
@@ -105,11 +109,15 @@ Layout layout(int64_t n, const splotch_camera *cam, const splotch_params *p, uin
     L.part_off = take(((size_t)L.n_tiles + 1) * 8);
     L.seg_scan = take(scan_u32_u64_scratch_bytes(L.n_tiles));
     L.item_tile = take(L.max_items * 4);
-    L.partial = take(L.max_slots * 6 * (size_t)L.tile * L.tile * 4);
     L.pk0 = take(cap * 4);
     L.pk1 = take(cap * 4);
     L.pv0 = take(cap * 4);
     L.pv1 = take(cap * 4);
+    // the sorts' scratch runs on over the partial images, which are written
+    // after them
+    L.radix = take(radix_scratch_bytes(std::max<size_t>(L.ordered ? N : 0, (size_t)cap)));
+    L.partial = take(L.max_slots * 6 * (size_t)L.tile * L.tile * 4);
+    L.radix_bytes = o - L.radix;
     L.total = o;
     return L;
 }
@@ -442,8 +450,13 @@ splotch_status run_order_and_scan(const Ctx &c, int64_t n, bool trim_keys,
         // without the read-back, the passes find the key range on the device
         const uint32_t *key_range =
             trim_keys ? nullptr : c.at<uint32_t>(c.L.range) + 2 * kMaxSpecies;
+        // the pair offsets are not written yet: the larger of their area and
+        // the pair sort's
+        const bool in_off = c.L.off_bytes > c.L.radix_bytes;
         TRY(radix_sort_pairs(k0, v0, k1, v1, true, (size_t)n, nullptr, bits, bias, false,
-                             c.at<void>(c.L.radix), &in1, c.s, tag ? cnt : nullptr, key_range));
+                             c.at<void>(in_off ? c.L.off : c.L.radix),
+                             in_off ? c.L.off_bytes : c.L.radix_bytes, &in1, c.s,
+                             tag ? cnt : nullptr, key_range));
         const uint32_t *ord = in1 ? v1 : v0;
         *order = ord;
         if (tag) {
@@ -499,7 +512,7 @@ splotch_status run_bin_chunk(const Ctx &c, const uint32_t *order, uint32_t idx_m
     while ((1ull << bits) < (uint64_t)c.L.n_tiles) ++bits;
     bool in1 = false;
     TRY(radix_sort_pairs(pk0, pv0, pk1, pv1, false, (size_t)npairs, nullptr, bits, 0u, true,
-                         c.at<void>(c.L.radix), &in1, c.s));
+                         c.at<void>(c.L.radix), c.L.radix_bytes, &in1, c.s));
     const uint32_t *keys = in1 ? pk1 : pk0;
     *vals = in1 ? pv1 : pv0;
     const uint32_t key_mask = e.qshift ? (1u << e.qshift) - 1u : 0xFFFFFFFFu;
@@ -735,7 +748,7 @@ splotch_status enqueue_view(Ctx &c, int32_t v, uint32_t *flags, uint64_t *totals
         while ((1ull << bits) < (uint64_t)Lv.n_tiles) ++bits;
         bool in1 = false;
         TRY(radix_sort_pairs(pk0, pv0, pk1, pv1, false, (size_t)cap, total, bits, 0u, true,
-                             c.at<void>(c.L.radix), &in1, c.s));
+                             c.at<void>(c.L.radix), c.L.radix_bytes, &in1, c.s));
         const uint32_t *keys = in1 ? pk1 : pk0;
         const uint32_t *vals = in1 ? pv1 : pv0;
         uint32_t *ts = c.at<uint32_t>(c.L.tstart), *te = c.at<uint32_t>(c.L.tend);

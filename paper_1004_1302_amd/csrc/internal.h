@@ -125,7 +125,8 @@ hipError_t launch_scan_u32(uint32_t *data, size_t n, void *scratch, hipStream_t 
 // (graph-capturable).  Buffers k0/v0 hold the input;
 // k1/v1 are the second half of the ping-pong.  *result_in_1 tells which
 // half holds the output.  keys_needed = false lets the last pass skip
-// writing keys.
+// writing keys.  scratch: at least radix_scratch_bytes(n), 256-byte aligned;
+// up to 2^20 keys sort faster with four times as much.
 size_t radix_scratch_bytes(size_t n);
 // tag_counts (with vals_identity, n <= 2^30): the identity values carry the
 // element's count from tag_counts in bits 30-31 (1, 2, 4; 0 = other), so a
@@ -135,8 +136,9 @@ size_t radix_scratch_bytes(size_t n);
 // of 8-bit digits from the range on the device, and the values land in v0.
 hipError_t radix_sort_pairs(uint32_t *k0, uint32_t *v0, uint32_t *k1, uint32_t *v1,
                             bool vals_identity, size_t n, const uint64_t *n_dev, int bits,
-                            uint32_t bias, bool keys_needed, void *scratch, bool *result_in_1,
-                            hipStream_t s, const uint32_t *tag_counts = nullptr,
+                            uint32_t bias, bool keys_needed, void *scratch, size_t scratch_bytes,
+                            bool *result_in_1, hipStream_t s,
+                            const uint32_t *tag_counts = nullptr,
                             const uint32_t *key_range = nullptr);
 constexpr int kTagShift = 30;
 constexpr uint32_t kIdxMask = (1u << kTagShift) - 1u;

@@ -1,8 +1,8 @@
 // splotch_render_static: splotch_render for callers that cannot allocate
 // device memory (code under HIP graph capture, tight serving loops,
 // harnesses that forbid allocation).  Its workspace is a file-scope device
-// array of SPLOTCH_STATIC_SCRATCH_BYTES and 1 MiB, one copy per GPU, held until
-// the process ends; the caller passes only the particles, palette and image.
+// array of SPLOTCH_STATIC_SCRATCH_BYTES, one copy per GPU, held until the
+// process ends; the caller passes only the particles, palette and image.
 #include <map>
 #include <mutex>
 
@@ -11,10 +11,7 @@
 
 namespace {
 
-// The 1 MiB is for the digit histograms of sorts of up to 2^20 keys: their short
-// tiles have up to 0.8 MB more of them than long ones, which does not count
-// against the particles.
-constexpr size_t kScratchBytes = SPLOTCH_STATIC_SCRATCH_BYTES + ((size_t)1 << 20);
+constexpr size_t kScratchBytes = SPLOTCH_STATIC_SCRATCH_BYTES;
 
 // The render's workspace for this entry point.  In host code `scratch`
 // names a host-side stand-in, never the device memory: host code uses only

@@ -591,22 +591,19 @@ hipError_t launch_scan_u32(uint32_t *data, size_t n, void *scratch, hipStream_t 
 // round of 256 after another; while 1024-key tiles still fit the GPU at once
 // (1024 workgroups, four a CU) the shorter chain wins: a pass of 2e4 keys
 // takes 10 us in them and 21 in 4096-key tiles.  From there on the longer
-// digit runs of 4096-key tiles do.
+// digit runs of 4096-key tiles do, and where the scratch has no room for the
+// short tiles' histogram, which has four times the columns.
 constexpr size_t kSmallSort = (size_t)1024 * kT * 4;
-constexpr int sort_ipt(size_t n) { return n <= kSmallSort ? 4 : kIpt; }
-size_t sort_tiles(size_t n) {
-    const size_t t = (size_t)kT * sort_ipt(n);
-    return (n + t - 1) / t;
+static size_t hist_bytes(size_t tiles) {
+    if (tiles == 0) tiles = 1;
+    return align_up(tiles * 256 * sizeof(uint32_t), 256) + scan_u32_scratch_bytes(tiles * 256);
+}
+static int sort_ipt(size_t n, size_t scratch_bytes) {
+    const size_t t = (size_t)kT * 4;
+    return n <= kSmallSort && hist_bytes((n + t - 1) / t) <= scratch_bytes ? 4 : kIpt;
 }
 
-size_t radix_scratch_bytes(size_t n) {
-    // the most tiles of any count up to n: below the step to large tiles,
-    // or at n
-    size_t nb = std::max(sort_tiles(n), sort_tiles(std::min(n, kSmallSort)));
-    if (nb == 0) nb = 1;
-    size_t hist = align_up(nb * 256 * sizeof(uint32_t), 256);
-    return hist + scan_u32_scratch_bytes(nb * 256);
-}
+size_t radix_scratch_bytes(size_t n) { return hist_bytes((n + kTile - 1) / kTile); }
 
 // One pass: digit histogram per tile, its scan, the scatter.  A count on
 // the device (n_dev) bounds the live tiles; the grid covers the capacity.
@@ -626,14 +623,16 @@ hipError_t radix_pass(const uint32_t *kin, const uint32_t *vin, uint32_t *kout, 
 
 hipError_t radix_sort_pairs(uint32_t *k0, uint32_t *v0, uint32_t *k1, uint32_t *v1,
                             bool vals_identity, size_t n, const uint64_t *n_dev, int bits,
-                            uint32_t bias, bool keys_needed, void *scratch, bool *result_in_1,
-                            hipStream_t s, const uint32_t *tag_counts,
+                            uint32_t bias, bool keys_needed, void *scratch, size_t scratch_bytes,
+                            bool *result_in_1, hipStream_t s, const uint32_t *tag_counts,
                             const uint32_t *key_range) {
     *result_in_1 = false;
     if (n == 0) return hipSuccess;
     if (key_range && (keys_needed || n_dev)) return hipErrorInvalidValue;
-    const uint32_t nb = (uint32_t)sort_tiles(n);
-    const bool small = sort_ipt(n) == 4;
+    if (scratch_bytes < radix_scratch_bytes(n)) return hipErrorInvalidValue;
+    const int ipt = sort_ipt(n, scratch_bytes);
+    const bool small = ipt == 4;
+    const uint32_t nb = (uint32_t)((n + (size_t)kT * ipt - 1) / ((size_t)kT * ipt));
     uint32_t *hist = reinterpret_cast<uint32_t *>(scratch);
     void *scan_scratch =
         reinterpret_cast<char *>(scratch) + align_up((size_t)nb * 256 * sizeof(uint32_t), 256);

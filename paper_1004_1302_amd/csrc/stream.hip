@@ -105,8 +105,9 @@ StreamLayout stream_layout(int64_t subset, int64_t slab, Fields f, size_t render
     L.key = take(S * 4);
     L.counters = take(kCntN * 8);
     L.range = take(kRangeSlots * 4);
-    L.partial = take(project_partial_words(subset) * 4);
-    L.flags = take(S * 4);
+    // the projection's partial words where the slab flags will be (88 bytes
+    // for 256 particles)
+    L.partial = L.flags = take(std::max(S * 4, project_partial_words(subset) * 4));
     L.pos = take(S * 4);
     L.scan = take(scan_u32_scratch_bytes(S));
     L.hist = take((size_t)kBins * 4);
