@@ -45,6 +45,10 @@ bool any_ordered(const splotch_params *p) {
     return false;
 }
 
+uint64_t default_capacity(int64_t n) {
+    return std::min(4ull * (uint64_t)n + 65536ull, (unsigned long long)kMaxPairCap);
+}
+
 // Lay out the workspace for n particles and pair capacity cap.
 Layout layout(int64_t n, const splotch_camera *cam, const splotch_params *p, uint64_t cap) {
     Layout L;
@@ -63,24 +67,13 @@ Layout layout(int64_t n, const splotch_camera *cam, const splotch_params *p, uin
         return at;
     };
     L.rec = take(N * sizeof(Rec));
-    L.cnt = take(N * 4);
     if (L.ordered) {
-        L.key0 = take(N * 4);
-        L.key1 = take(N * 4);
         L.val0 = take(N * 4);
         L.val1 = take(N * 4);
     }
     // the projection's partial words (88 bytes for 256 particles) come first
     L.off = take(std::max((N + 1) * 8, project_partial_words(n) * 4));
     L.off_bytes = o - L.off;
-    // split particles: a queue part and a count per emission workgroup and
-    // the counts' scan (the dense queue reuses cnt, which the pair-offset
-    // scan has consumed by then, and the scan's scratch that of that scan)
-    const size_t emit_groups = (N + kEmitGroup - 1) / kEmitGroup;
-    L.split = take(emit_groups * kEmitGroup * 4);
-    L.split_cnt = take(emit_groups * 4);
-    L.split_off = take((emit_groups + 1) * 8);
-    L.scan = take(scan_u32_u64_scratch_bytes(N));
     L.counters = take(kCntN * 8);
     L.range = take(kRangeSlots * 4);
     // split_total, in the bounds' last 256 bytes, and the tile ranges are
@@ -92,13 +85,8 @@ Layout layout(int64_t n, const splotch_camera *cam, const splotch_params *p, uin
     L.tend = take((size_t)L.n_tiles * 4);
     L.mcount = take((size_t)L.n_tiles * 16);
     // segments: seg_len >= pairs / kSegTarget keeps the number of items <=
-    // n_tiles + kSegTarget; a tile of L > seg_len records has
-    // ceil(L / seg_len) < 2 L / seg_len segments, so the partial slots of a
-    // pass number < 2 pairs / seg_len
+    // n_tiles + kSegTarget
     L.max_items = (uint64_t)L.n_tiles + kSegTarget + 64;
-    L.max_slots = std::min<uint64_t>(
-        2 * kSegTarget,
-        2 * seg_bound(cap, (uint32_t)(L.tile * L.tile), (uint32_t)p->seg_records) + 2);
     L.seg_len = take(4);
     L.flags = take((size_t)SPLOTCH_MAX_VIEWS * 12);  // per view: overflow flag (u32), pairs (u64)
     L.sargs = take(kMaxGroup * sizeof(SplatArgs));    // splat settings of a persistent group
@@ -109,15 +97,37 @@ Layout layout(int64_t n, const splotch_camera *cam, const splotch_params *p, uin
     L.part_off = take(((size_t)L.n_tiles + 1) * 8);
     L.seg_scan = take(scan_u32_u64_scratch_bytes(L.n_tiles));
     L.item_tile = take(L.max_items * 4);
+    // the sorted pairs (run_pair_sort)
     L.pk0 = take(cap * 4);
-    L.pk1 = take(cap * 4);
     L.pv0 = take(cap * 4);
+    // From here on nothing is in use while a pass is splatted and merged: the
+    // counts (consumed by the pair-offset scan), the depth keys, the emission's
+    // queues, the scans' and sorts' scratch and the sort's other halves.  The
+    // partial images take all of it, beside the slots of their own that hold
+    // the segments which every pass may have; shorter segments in what
+    // is left cost no pair capacity.
+    L.partial = o;
+    L.cnt = take(N * 4);
+    if (L.ordered) {
+        L.key0 = take(N * 4);
+        L.key1 = take(N * 4);
+    }
+    // split particles: a queue part and a count per emission workgroup and
+    // the counts' scan (the dense queue reuses cnt, which the pair-offset
+    // scan has consumed by then, and the scan's scratch that of that scan)
+    const size_t emit_groups = (N + kEmitGroup - 1) / kEmitGroup;
+    L.split = take(emit_groups * kEmitGroup * 4);
+    L.split_cnt = take(emit_groups * 4);
+    L.split_off = take((emit_groups + 1) * 8);
+    L.scan = take(scan_u32_u64_scratch_bytes(N));
+    L.pk1 = take(cap * 4);
     L.pv1 = take(cap * 4);
-    // the sorts' scratch runs on over the partial images, which are written
-    // after them
+    // the sorts' scratch runs on over the slots
+    const size_t slot = 6 * (size_t)L.tile * L.tile * 4;
     L.radix = take(radix_scratch_bytes(std::max<size_t>(L.ordered ? N : 0, (size_t)cap)));
-    L.partial = take(L.max_slots * 6 * (size_t)L.tile * L.tile * 4);
+    take(seg_slots_sure(cap, (uint32_t)p->seg_records) * slot);
     L.radix_bytes = o - L.radix;
+    L.max_slots = (o - L.partial) / slot;
     L.total = o;
     return L;
 }
@@ -364,7 +374,7 @@ struct Ctx {
     char *ws;
     hipStream_t s;
     uint64_t split = 0;  // split threshold in pixels, 0 = no splitting
-    uint32_t seg_min = 0;  // the caller's least records per segment, 0 = by the pairs
+    SegRule seg = {};
     const uint8_t *tile_mask = nullptr;
     Prof prof;
     template <typename T>
@@ -476,13 +486,38 @@ splotch_status run_order_and_scan(const Ctx &c, int64_t n, bool trim_keys,
     return SPLOTCH_OK;
 }
 
+// The sort of a pass' pairs by the bits of their tile index leaves them in
+// (pk0, pv0), so it starts in the other halves where its passes are odd in
+// number.
+int tile_bits(uint32_t n_tiles) {
+    int bits = 0;
+    while ((1ull << bits) < (uint64_t)n_tiles) ++bits;
+    return bits;
+}
+
+void pair_input(const Ctx &c, uint32_t n_tiles, uint32_t **key, uint32_t **val) {
+    const bool odd = radix_passes(tile_bits(n_tiles)) & 1;
+    *key = c.at<uint32_t>(odd ? c.L.pk1 : c.L.pk0);
+    *val = c.at<uint32_t>(odd ? c.L.pv1 : c.L.pv0);
+}
+
+hipError_t run_pair_sort(const Ctx &c, uint32_t n_tiles, size_t n, const uint64_t *n_dev) {
+    uint32_t *k, *v;
+    pair_input(c, n_tiles, &k, &v);
+    uint32_t *pk0 = c.at<uint32_t>(c.L.pk0), *pv0 = c.at<uint32_t>(c.L.pv0);
+    const bool odd = k != pk0;
+    bool in1 = false;
+    return radix_sort_pairs(k, v, odd ? pk0 : c.at<uint32_t>(c.L.pk1),
+                            odd ? pv0 : c.at<uint32_t>(c.L.pv1), false, n, n_dev,
+                            tile_bits(n_tiles), 0u, true, c.at<void>(c.L.radix), c.L.radix_bytes,
+                            &in1, c.s);
+}
+
 // Bin one chunk [first, last) of processing positions: emit, sort by tile,
 // tile ranges.  Returns the sorted pair values via *vals.
 splotch_status run_bin_chunk(const Ctx &c, const uint32_t *order, uint32_t idx_mask,
                              uint64_t first, uint64_t last, uint64_t off_first, uint64_t npairs,
                              const uint32_t **vals, const uint32_t **keys_out = nullptr) {
-    uint32_t *pk0 = c.at<uint32_t>(c.L.pk0), *pk1 = c.at<uint32_t>(c.L.pk1);
-    uint32_t *pv0 = c.at<uint32_t>(c.L.pv0), *pv1 = c.at<uint32_t>(c.L.pv1);
     EmitArgs e;
     e.rec = c.at<Rec>(c.L.rec);
     e.order = order;
@@ -497,8 +532,7 @@ splotch_status run_bin_chunk(const Ctx &c, const uint32_t *order, uint32_t idx_m
     e.tile = c.L.tile;
     e.qshift = block_mask_shift(c.L.tile, c.L.n_tiles);
     e.ntx = c.L.ntx;
-    e.pair_key = pk0;
-    e.pair_val = pv0;
+    pair_input(c, c.L.n_tiles, &e.pair_key, &e.pair_val);
     e.split_pixels = c.split;
     e.split_list = c.split ? c.at<uint32_t>(c.L.split) : nullptr;
     e.split_count = c.at<uint32_t>(c.L.split_cnt);
@@ -508,13 +542,9 @@ splotch_status run_bin_chunk(const Ctx &c, const uint32_t *order, uint32_t idx_m
     e.split_total = c.at<uint32_t>(c.L.split_total);
     TRY(launch_emit(e, c.s));
     TRY(const_cast<Prof &>(c.prof).mark(3));
-    int bits = 0;
-    while ((1ull << bits) < (uint64_t)c.L.n_tiles) ++bits;
-    bool in1 = false;
-    TRY(radix_sort_pairs(pk0, pv0, pk1, pv1, false, (size_t)npairs, nullptr, bits, 0u, true,
-                         c.at<void>(c.L.radix), c.L.radix_bytes, &in1, c.s));
-    const uint32_t *keys = in1 ? pk1 : pk0;
-    *vals = in1 ? pv1 : pv0;
+    TRY(run_pair_sort(c, c.L.n_tiles, (size_t)npairs, nullptr));
+    const uint32_t *keys = c.at<uint32_t>(c.L.pk0);
+    *vals = c.at<uint32_t>(c.L.pv0);
     const uint32_t key_mask = e.qshift ? (1u << e.qshift) - 1u : 0xFFFFFFFFu;
     TRY(launch_tile_ranges(keys, (size_t)npairs, nullptr, c.at<uint32_t>(c.L.tstart),
                            c.at<uint32_t>(c.L.tend), c.L.n_tiles, key_mask,
@@ -548,9 +578,8 @@ splotch_status plan_chunks(const Ctx &c, int64_t n, std::vector<uint64_t> *plan)
 }
 
 splotch_status run_splat_pass(Ctx &c, SplatArgs &sa, uint64_t npairs) {
-    const uint32_t nt = (uint32_t)(c.L.tile * c.L.tile);
-    const uint32_t seg_len = seg_len_rule(npairs, nt, c.seg_min);
-    TRY(launch_segments(sa.tile_start, sa.tile_end, c.L.n_tiles, npairs, nullptr, nt, c.seg_min,
+    const uint32_t seg_len = seg_len_rule(npairs, c.seg.nt, c.seg.seg_min);  // the least
+    TRY(launch_segments(sa.tile_start, sa.tile_end, c.L.n_tiles, npairs, nullptr, c.seg,
                         c.at<uint32_t>(c.L.seg_len), c.at<uint32_t>(c.L.nseg),
                         c.at<uint32_t>(c.L.nmulti), c.at<uint64_t>(c.L.seg_off),
                         c.at<uint64_t>(c.L.part_off), c.at<uint32_t>(c.L.item_tile),
@@ -628,7 +657,13 @@ splotch_status prepare(const splotch_particles *P, const splotch_camera *cam,
     if (!fit_capacity(P->n, cam, p, p->workspace_bytes, &c->L)) return SPLOTCH_E_WORKSPACE;
     c->ws = reinterpret_cast<char *>(p->workspace);
     c->s = reinterpret_cast<hipStream_t>(p->stream);
-    c->seg_min = (uint32_t)p->seg_records;
+    c->seg.nt = (uint32_t)(c->L.tile * c->L.tile);
+    c->seg.seg_min = (uint32_t)p->seg_records;
+    // No more than the slots of the default pair capacity: the segments, and
+    // with them an image's rounding, are then the same in every workspace of
+    // at least that.
+    c->seg.slots = std::min(c->L.max_slots,
+                            layout(P->n, cam, p, default_capacity(P->n)).max_slots);
     c->tile_mask = p->tile_mask;
     c->split = split_threshold(p, cam);
     if (c->prof.start(p->profile != 0 && p->stats != nullptr, c->s) != hipSuccess)
@@ -695,7 +730,6 @@ splotch_status enqueue_view(Ctx &c, int32_t v, uint32_t *flags, uint64_t *totals
                             splotch_image *image, SplatArgs *defer = nullptr) {
     const int64_t n = P->n;
     const uint64_t cap = c.L.pair_cap;
-    const uint32_t nt = (uint32_t)(c.L.tile * c.L.tile);
     {
         Layout Lv = c.L;  // same buffers; per-view tile grid
         Lv.ntx = (cam->width + c.L.tile - 1) / c.L.tile;
@@ -705,7 +739,7 @@ splotch_status enqueue_view(Ctx &c, int32_t v, uint32_t *flags, uint64_t *totals
         cv.L = Lv;
         cv.ws = c.ws;
         cv.s = c.s;
-        cv.seg_min = c.seg_min;
+        cv.seg = c.seg;
         cv.tile_mask = c.tile_mask;
         splotch_status st;
         // the value range does not depend on the camera: the projection of
@@ -737,25 +771,17 @@ splotch_status enqueue_view(Ctx &c, int32_t v, uint32_t *flags, uint64_t *totals
         e.split_scratch = c.at<void>(c.L.scan);
         e.split_dense = c.at<uint32_t>(c.L.cnt);
         e.split_total = c.at<uint32_t>(c.L.split_total);
-        uint32_t *pk0 = c.at<uint32_t>(c.L.pk0), *pk1 = c.at<uint32_t>(c.L.pk1);
-        uint32_t *pv0 = c.at<uint32_t>(c.L.pv0), *pv1 = c.at<uint32_t>(c.L.pv1);
-        e.pair_key = pk0;
-        e.pair_val = pv0;
+        pair_input(c, Lv.n_tiles, &e.pair_key, &e.pair_val);
         TRY(launch_emit(e, c.s));
         hipLaunchKernelGGL(k_copy_u64, dim3(1), dim3(64), 0, c.s, total, totals + v);
         TRY(hipGetLastError());
-        int bits = 0;
-        while ((1ull << bits) < (uint64_t)Lv.n_tiles) ++bits;
-        bool in1 = false;
-        TRY(radix_sort_pairs(pk0, pv0, pk1, pv1, false, (size_t)cap, total, bits, 0u, true,
-                             c.at<void>(c.L.radix), c.L.radix_bytes, &in1, c.s));
-        const uint32_t *keys = in1 ? pk1 : pk0;
-        const uint32_t *vals = in1 ? pv1 : pv0;
+        TRY(run_pair_sort(c, Lv.n_tiles, (size_t)cap, total));
+        const uint32_t *keys = c.at<uint32_t>(c.L.pk0), *vals = c.at<uint32_t>(c.L.pv0);
         uint32_t *ts = c.at<uint32_t>(c.L.tstart), *te = c.at<uint32_t>(c.L.tend);
         TRY(launch_tile_ranges(keys, (size_t)cap, total, ts, te, Lv.n_tiles,
                                e.qshift ? (1u << e.qshift) - 1u : 0xFFFFFFFFu,
                                c.at<uint32_t>(c.L.split_total), c.s));
-        TRY(launch_segments(ts, te, Lv.n_tiles, cap, total, nt, c.seg_min,
+        TRY(launch_segments(ts, te, Lv.n_tiles, cap, total, c.seg,
                             c.at<uint32_t>(c.L.seg_len), c.at<uint32_t>(c.L.nseg),
                             c.at<uint32_t>(c.L.nmulti), c.at<uint64_t>(c.L.seg_off),
                             c.at<uint64_t>(c.L.part_off), c.at<uint32_t>(c.L.item_tile),
@@ -940,8 +966,8 @@ splotch_status splotch_workspace_size(int64_t n, const splotch_camera *cam,
     splotch_status st;
     if ((st = validate_camera(cam)) != SPLOTCH_OK) return st;
     if ((st = validate_params(params)) != SPLOTCH_OK) return st;
-    uint64_t cap = max_pairs > 0 ? (uint64_t)max_pairs : 4ull * (uint64_t)n + 65536ull;
-    if (cap > kMaxPairCap) cap = kMaxPairCap;
+    const uint64_t cap = max_pairs > 0 ? std::min((uint64_t)max_pairs, kMaxPairCap)
+                                       : default_capacity(n);
     *bytes = layout(n, cam, params, cap).total;
     return SPLOTCH_OK;
 }
@@ -1117,7 +1143,7 @@ splotch_status splotch_render_batch(const splotch_particles *P, int32_t n_views,
         lanes[k].L = c.L;
         lanes[k].ws = c.ws + (size_t)k * q.workspace_bytes;
         lanes[k].s = k == 0 ? c.s : ls->s[k - 1];
-        lanes[k].seg_min = c.seg_min;
+        lanes[k].seg = c.seg;
         lanes[k].tile_mask = c.tile_mask;
         lanes[k].split = c.split;
     }

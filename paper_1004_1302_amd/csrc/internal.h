@@ -128,6 +128,7 @@ hipError_t launch_scan_u32(uint32_t *data, size_t n, void *scratch, hipStream_t 
 // writing keys.  scratch: at least radix_scratch_bytes(n), 256-byte aligned;
 // up to 2^20 keys sort faster with four times as much.
 size_t radix_scratch_bytes(size_t n);
+inline int radix_passes(int bits) { return bits <= 0 ? 1 : (bits + 7) / 8; }
 // tag_counts (with vals_identity, n <= 2^30): the identity values carry the
 // element's count from tag_counts in bits 30-31 (1, 2, 4; 0 = other), so a
 // sorted order also gives the counts in that order without a gather.
@@ -244,18 +245,23 @@ struct SplatArgs {
 };
 // How a workgroup walks a tile's list.
 constexpr int kSplatBox = 0, kSplatRows = 1, kSplatLists = 2;
-// Segment length rule (shared by host and device; nt: pixels of a tile): at
-// least pairs / kSegTarget, so that a pass has at most n_tiles + kSegTarget
-// items, and a multiple of nt at least the caller's seg_min.
+// Segment length rule (shared by host and device): at least pairs /
+// kSegTarget, so that a pass has at most n_tiles + kSegTarget items, and a
+// multiple of nt at least the caller's seg_min.
 // Without one (seg_min = 0) the least length follows the pairs: a list is
 // walked record by record, so where a pass has fewer items than the GPU has
 // room for, its longest list is what it waits for.  A segment then holds
-// 1 / kSegFill(nt) of the pairs (8192 waves of 8x8 blocks, the GPU's 256 CUs
+// 1 / seg_fill(nt) of the pairs (8192 waves of 8x8 blocks, the GPU's 256 CUs
 // hold 6144), from 128 records (below, a segment's setup and its partial image
-// cost what the shorter walk saves) to 1024 (or nt), which was the least for
-// all: the splat of 1e5 particles at 256 x 256 pixels takes 18 us, 74 with it.
+// cost what the shorter walk saves) to 1024 (or nt): the splat of 1e5
+// particles at 256 x 256 pixels takes 18 us, 74 with 1024 as the least.
 constexpr uint64_t kSegTarget = 65536;
 constexpr uint32_t kSegLow = 128, kSegHigh = 1024;
+struct SegRule {
+    uint32_t nt;       // pixels of a tile
+    uint32_t seg_min;  // the caller's least records per segment, 0 = by the pairs
+    uint64_t slots;    // partial images a pass may use beyond seg_slots_sure
+};
 __host__ __device__ inline uint64_t seg_fill(uint32_t nt) { return 524288u / nt; }
 __host__ __device__ inline uint32_t seg_len_rule(uint64_t npairs, uint32_t nt, uint32_t seg_min) {
     uint64_t s = (npairs + kSegTarget - 1) / kSegTarget;
@@ -271,21 +277,33 @@ __host__ __device__ inline uint32_t seg_len_rule(uint64_t npairs, uint32_t nt, u
     }
     return (uint32_t)(s < 0x7FFFFFFFull ? s : 0x7FFFFFFFull);
 }
-// Bound on pairs / seg_len_rule for passes of at most cap pairs: the least
-// lengths give cap / seg_min, or the fill while segments are shorter than
-// kSegHigh (from kSegLow) and cap / kSegHigh beyond.
-inline uint64_t seg_bound(uint64_t cap, uint32_t nt, uint32_t seg_min) {
-    if (seg_min) return cap / seg_min;
-    const uint64_t fill = seg_fill(nt), low = cap / kSegLow;
-    const uint64_t part = low < fill ? low : fill, whole = cap / kSegHigh;
-    return part > whole ? part : whole;
+// Partial images that the workspace always holds for a pass of npairs: those
+// of segments of seg_min (0: kSegHigh) records.  A tile of L > s records has
+// ceil(L / s) < 2 L / s segments of s, so a pass uses fewer than 2 npairs / s.
+__host__ __device__ inline uint64_t seg_slots_sure(uint64_t npairs, uint32_t seg_min) {
+    const uint64_t n = 2 * (npairs / (seg_min ? seg_min : kSegHigh)) + 2;
+    return n < 2 * kSegTarget ? n : 2 * kSegTarget;
+}
+// Partial images a pass of npairs may use, and the least segment length whose
+// images surely fit: the rule's own where a seg_min is given.
+__host__ __device__ inline uint64_t seg_slots(uint64_t npairs, const SegRule &r) {
+    const uint64_t sure = seg_slots_sure(npairs, r.seg_min);
+    return r.slots > sure ? r.slots : sure;
+}
+__host__ __device__ inline uint32_t seg_len_fits(uint64_t npairs, const SegRule &r) {
+    const uint32_t low = seg_len_rule(npairs, r.nt, r.seg_min);
+    if (r.seg_min) return low;
+    const uint64_t slots = seg_slots(npairs, r);
+    uint64_t s = (2 * npairs + slots - 1) / slots;
+    s = (s + 63) / 64 * 64;
+    return s > low ? (uint32_t)(s < 0x7FFFFFFFull ? s : 0x7FFFFFFFull) : low;
 }
 // Segment bookkeeping for one pass: segment length (from the pair count,
 // host value or device pointer), counts per tile, their scans and the
 // item -> tile map.  scratch: scan_u32_u64_scratch_bytes(n_tiles).
 hipError_t launch_segments(const uint32_t *tile_start, const uint32_t *tile_end,
                            uint32_t n_tiles, uint64_t npairs, const uint64_t *npairs_dev,
-                           uint32_t nt, uint32_t seg_min, uint32_t *seg_len, uint32_t *nseg,
+                           const SegRule &rule, uint32_t *seg_len, uint32_t *nseg,
                            uint32_t *nmulti, uint64_t *seg_off, uint64_t *part_off,
                            uint32_t *item_tile, uint64_t max_items, void *scratch,
                            hipStream_t s);

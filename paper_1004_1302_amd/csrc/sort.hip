@@ -637,7 +637,7 @@ hipError_t radix_sort_pairs(uint32_t *k0, uint32_t *v0, uint32_t *k1, uint32_t *
     void *scan_scratch =
         reinterpret_cast<char *>(scratch) + align_up((size_t)nb * 256 * sizeof(uint32_t), 256);
     if (key_range) bits = 32;  // the passes the range needs are found on the device
-    const int passes = bits <= 0 ? 1 : (bits + 7) / 8;
+    const int passes = radix_passes(bits);
     // 7-bit digits when they cover the key in as many passes: half the
     // histogram, and digit runs twice as long in the scatter's writes
     const int db = !key_range && bits > 0 && bits <= 7 * passes ? 7 : 8;

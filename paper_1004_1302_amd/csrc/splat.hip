@@ -1223,12 +1223,11 @@ __global__ __launch_bounds__(T *T < 1024 ? T *T : 1024) void k_merge(SplatArgs a
 }
 
 __global__ void k_seg_count(const uint32_t *ts, const uint32_t *te, uint32_t n_tiles,
-                            uint64_t npairs, const uint64_t *npairs_dev, uint32_t nt,
-                            uint32_t seg_min, uint32_t *seg_len_out, uint32_t *nseg,
-                            uint32_t *nmulti) {
+                            uint64_t npairs, const uint64_t *npairs_dev, SegRule rule,
+                            uint32_t *seg_len_out, uint32_t *nseg, uint32_t *nmulti) {
     const uint32_t t = blockIdx.x * blockDim.x + threadIdx.x;
     const uint64_t np = npairs_dev ? (*npairs_dev < npairs ? *npairs_dev : npairs) : npairs;
-    const uint32_t seg_len = seg_len_rule(np, nt, seg_min);
+    const uint32_t seg_len = seg_len_fits(np, rule);
     if (t == 0) *seg_len_out = seg_len;
     if (t >= n_tiles) return;
     const uint32_t len = te[t] - ts[t];
@@ -1247,13 +1246,35 @@ constexpr uint32_t kOneGroupTiles = 8192;
 constexpr uint32_t kOwnItems = 8;  // items a lane writes by itself
 __global__ __launch_bounds__(1024) void k_segments_small(
     const uint32_t *ts, const uint32_t *te, uint32_t n_tiles, uint64_t npairs,
-    const uint64_t *npairs_dev, uint32_t nt, uint32_t seg_min, uint32_t *seg_len_out,
-    uint64_t *seg_off, uint64_t *part_off, uint32_t *item_tile, uint64_t max_items) {
+    const uint64_t *npairs_dev, SegRule rule, uint32_t *seg_len_out, uint64_t *seg_off,
+    uint64_t *part_off, uint32_t *item_tile, uint64_t max_items) {
     __shared__ uint32_t s_n[16], s_m[16];
     const uint64_t np = npairs_dev ? (*npairs_dev < npairs ? *npairs_dev : npairs) : npairs;
-    const uint32_t seg_len = seg_len_rule(np, nt, seg_min);
-    if (threadIdx.x == 0) *seg_len_out = seg_len;
     const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+    // The shortest length whose partial images fit: those of most lists are
+    // about half the bound, so lengths between the rule's and the sure one are
+    // tried on the lists themselves (at most 10, only where the rule's does not
+    // surely fit).
+    const uint32_t fits = seg_len_fits(np, rule);
+    uint32_t seg_len = seg_len_rule(np, rule.nt, rule.seg_min);
+    while (seg_len < fits) {
+        uint32_t m = 0;
+        for (uint32_t t = threadIdx.x; t < n_tiles; t += 1024) {
+            const uint32_t len = te[t] - ts[t];
+            if (len > seg_len) m += (len + seg_len - 1) / seg_len;
+        }
+        for (int o = 32; o > 0; o >>= 1) m += (uint32_t)__shfl_xor((int)m, o, 64);
+        if (lane == 0) s_m[wave] = m;
+        __syncthreads();
+        uint64_t used = 0;
+#pragma unroll
+        for (uint32_t k = 0; k < 16; ++k) used += s_m[k];
+        __syncthreads();
+        if (used <= seg_slots(np, rule)) break;
+        const uint32_t next = (seg_len + seg_len / 4 + 63) / 64 * 64;
+        seg_len = next < fits ? next : fits;
+    }
+    if (threadIdx.x == 0) *seg_len_out = seg_len;
     uint64_t cn = 0, cm = 0;  // items and partial slots of the tiles before
     auto tile_len = [&](uint32_t t) {
         const uint32_t q = t < n_tiles ? t : n_tiles - 1;
@@ -1496,19 +1517,19 @@ uint32_t splat_grid(uint32_t n_tiles, uint64_t npairs, uint32_t seg_len) {
 
 hipError_t launch_segments(const uint32_t *tile_start, const uint32_t *tile_end,
                            uint32_t n_tiles, uint64_t npairs, const uint64_t *npairs_dev,
-                           uint32_t nt, uint32_t seg_min, uint32_t *seg_len, uint32_t *nseg,
+                           const SegRule &rule, uint32_t *seg_len, uint32_t *nseg,
                            uint32_t *nmulti, uint64_t *seg_off, uint64_t *part_off,
                            uint32_t *item_tile, uint64_t max_items, void *scratch,
                            hipStream_t s) {
     if (n_tiles <= kOneGroupTiles) {
         hipLaunchKernelGGL(k_segments_small, dim3(1), dim3(1024), 0, s, tile_start, tile_end,
-                           n_tiles, npairs, npairs_dev, nt, seg_min, seg_len, seg_off, part_off,
+                           n_tiles, npairs, npairs_dev, rule, seg_len, seg_off, part_off,
                            item_tile, max_items);
         return hipGetLastError();
     }
     const uint32_t g = (n_tiles + 255) / 256;
     hipLaunchKernelGGL(k_seg_count, dim3(g), dim3(256), 0, s, tile_start, tile_end, n_tiles,
-                       npairs, npairs_dev, nt, seg_min, seg_len, nseg, nmulti);
+                       npairs, npairs_dev, rule, seg_len, nseg, nmulti);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if ((e = launch_scan_u32_u64(nseg, seg_off, n_tiles, scratch, s)) != hipSuccess) return e;

@@ -49,3 +49,32 @@ def test_smallest_workspace(n, tile):
                                         workspace=ws)
     assert total1 == total
     assert torch.equal(ts1, ts) and torch.equal(te1, te) and torch.equal(pp1, pp)
+
+
+@pytest.mark.parametrize("tile,width", [(8, 150), (16, 150), (32, 150), (64, 150), (8, 800)])
+@pytest.mark.parametrize("n", [300, 20_000, 150_000])
+def test_default_segments_where_slots_are_few(n, tile, width):
+    """The default segments in workspaces from the one for exactly the pairs,
+    whose slots allow only longer segments, to the default one (15,200 tiles
+    of 8 pixels: the bookkeeping in four kernels).  An additive set: the
+    partial images and their compensated sum round a pixel's positive sum by
+    2^-24 a few times, and the terms of a 64-record batch, which begin
+    elsewhere in a list with every cut, are added plainly: 2 x 64 x 2^-24 =
+    7.7e-6 of a pixel's value."""
+    import torch
+    scene = synth.plummer_mix(n, seed=n)
+    parts, pal = B.scene_to_device(scene)
+    cam = synth.ortho_unit_square(width, width * 3 // 4 if width < 800 else 1200)
+    kw = dict(compensated=True, tile=tile)
+    one, st = B.render(parts, cam, pal, scene.species_params, seg_records=1 << 24, stats=True,
+                       max_pairs=20 * n + 200_000, **kw)
+    assert st["n_chunks"] == 1
+    total = st["n_pairs"]
+    scene.camera = cam
+    assert float(one.max()) > 0
+    for pairs in (total, total + total // 8, 2 * total, 0):
+        img, st = B.render(parts, cam, pal, scene.species_params, stats=True,
+                           workspace=workspace(scene, pairs, tile=tile), **kw)
+        assert st["n_chunks"] == 1 or pairs == 0
+        assert float((img - one).abs().max()) <= 1e-5 * float(one.max())
+        assert bool(((img - one).abs() <= 1e-5 * one).all())

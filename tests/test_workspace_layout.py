@@ -44,3 +44,14 @@ def test_stream_workspace_does_not_grow(n, subset, slab, most):
     assert B.lib().splotch_stream_workspace_size(C.byref(P), subset, slab, C.byref(cam),
                                                  C.byref(prm), C.byref(out)) == 0
     assert out.value <= most
+
+
+@pytest.mark.parametrize("n,w,h,tile,nbytes,least", [
+    (4_000_000, 1920, 1080, 16, 256 << 20, 373_759), (4_000_000, 1024, 1024, 32, 256 << 20, 168_959),
+    (1_000_000, 1024, 1024, 16, 80_000_000, 540_671),
+    (1_000_000, 1024, 1024, 16, 100_000_000, 1_252_352),
+    (1_000_000, 1024, 1024, 8, 80_000_000, 763_136), (2_000, 4096, 4096, 64, 8 << 20, 36_863),
+    (100_000, 256, 256, 16, 12_000_000, 185_216)])
+def test_workspace_holds_as_many_pairs(n, w, h, tile, nbytes, least):
+    """With the default segments: `least` pairs and the layout for them fit."""
+    assert size(n, w, h, tile, 1, least) <= nbytes
