@@ -187,7 +187,7 @@ typedef struct splotch_params {
     int32_t seg_records; /* least records per tile-list segment (one workgroup
                             each); 0 = 128 to 1024 (64 px tiles: to 4096) by
                             the number of pairs.  Long lists are cut into segments
-                            whose partial (C, T) are merged front to back:
+                            whose partial (C, L) are merged front to back:
                             this changes speed and, within rounding, how a
                             tile's sums are associated. */
     int32_t splat_variant; /* how a tile's list is walked (speed only, the

@@ -208,7 +208,7 @@ hipError_t launch_chunk_plan(const uint64_t *off, uint64_t n, uint64_t capacity,
 
 // Splat.  Work items are (tile, segment): each tile's list is cut into
 // segments of at most seg_len records; a tile with one segment writes its
-// pixels directly, a tile with several writes one partial (C, Tr) per
+// pixels directly, a tile with several writes one partial (C, L) per
 // segment that the merge kernel folds front to back.
 struct SplatArgs {
     const Rec *rec;
@@ -219,7 +219,7 @@ struct SplatArgs {
     const uint64_t *seg_off;    // [n_tiles + 1] first item of each tile
     const uint64_t *part_off;   // [n_tiles + 1] first partial slot of each multi-segment tile
     const uint32_t *item_tile;  // item -> tile
-    float *partial;             // [slot][6][T*T]: C0 C1 C2 Tr0 Tr1 Tr2
+    float *partial;             // [slot][6][T*T]: C0 C1 C2 L0 L1 L2 (optical depths)
     uint64_t max_slots;         // partial slots in the buffer
     uint64_t max_items;         // entries of item_tile
     const uint32_t *seg_len;    // device: records per segment for this pass

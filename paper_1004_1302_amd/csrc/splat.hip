@@ -544,9 +544,9 @@ __global__ __launch_bounds__(T *T) void k_splat_lists(SplatArgs a) {
         slot[1 * NT + tid] = px.C1;
         slot[2 * NT + tid] = px.C2;
         if (ORDERED) {
-            slot[3 * NT + tid] = T0;
-            slot[4 * NT + tid] = T1;
-            slot[5 * NT + tid] = T2;
+            slot[3 * NT + tid] = px.L0;
+            slot[4 * NT + tid] = px.L1;
+            slot[5 * NT + tid] = px.L2;
         }
     }
 }
@@ -822,9 +822,9 @@ __device__ __forceinline__ void rows_unit(const SplatArgs &a, uint32_t item, uin
         slot[1 * NT + p] = px.C1;
         slot[2 * NT + p] = px.C2;
         if (ORDERED) {
-            slot[3 * NT + p] = T0;
-            slot[4 * NT + p] = T1;
-            slot[5 * NT + p] = T2;
+            slot[3 * NT + p] = px.L0;
+            slot[4 * NT + p] = px.L1;
+            slot[5 * NT + p] = px.L2;
         }
     }
 }
@@ -1164,17 +1164,31 @@ __global__ __launch_bounds__(64) void k_splat_box(SplatArgs a) {
             slot[1 * NT + p] = C1;
             slot[2 * NT + p] = C2;
             if (ORDERED) {
-                slot[3 * NT + p] = T0;
-                slot[4 * NT + p] = T1;
-                slot[5 * NT + p] = T2;
+                slot[3 * NT + p] = px.L0;
+                slot[4 * NT + p] = px.L1;
+                slot[5 * NT + p] = px.L2;
             }
         }
     }
 }
 
-// Fold the partial (C, Tr) of a multi-segment tile front to back:
-// C += Tr * C_s, Tr *= Tr_s (the associative "over"); a plain sum when
-// nothing absorbs.
+// Fold the partial (C, L) of a multi-segment tile front to back:
+// C += exp(-L) C_s, L += L_s (the associative "over"); a plain sum when
+// nothing absorbs.  The optical depths are summed compensated and their
+// exponential is taken of the sum, so the transmittance behind any number of
+// segments carries the error of one exponential; a product of the segments'
+// rounded transmittances would gain 2^-24 with each (1e-5 behind 1024).
+//
+// behind: adds a segment's optical depth to (L, M) and gives the transmittance
+// T = exp(-(L - M)).  A depth above 256 (exp(-104) is 0) counts as 256, so an
+// infinite one stays out of the compensation; NaN stays NaN.
+__device__ __forceinline__ void behind(float &L, float &M, float &T, float l) {
+#pragma clang fp contract(off)
+    kahan_step(L, M, (l > 256.f ? 256.f : l) - M);
+    T = expf(-L);
+    T = __builtin_fmaf(T, M, T);
+}
+
 template <int T, bool ORDERED, bool KAHAN>
 __global__ __launch_bounds__(T *T < 1024 ? T *T : 1024) void k_merge(SplatArgs a) {
     constexpr int NT = T * T;
@@ -1188,15 +1202,16 @@ __global__ __launch_bounds__(T *T < 1024 ? T *T : 1024) void k_merge(SplatArgs a
         const int i = tx * T + (p % T), j = ty * T + (p / T);
         float C0 = 0.f, C1 = 0.f, C2 = 0.f, K0 = 0.f, K1 = 0.f, K2 = 0.f;
         float T0 = 1.f, T1 = 1.f, T2 = 1.f;
+        float L0 = 0.f, L1 = 0.f, L2 = 0.f, M0 = 0.f, M1 = 0.f, M2 = 0.f;
         const float *slot = a.partial + (size_t)a.part_off[tile] * 6 * NT + p;
         auto over = [&](const float *v) {
             add_term<ORDERED, KAHAN>(C0, K0, T0, v[0]);
             add_term<ORDERED, KAHAN>(C1, K1, T1, v[1]);
             add_term<ORDERED, KAHAN>(C2, K2, T2, v[2]);
             if (ORDERED) {
-                T0 *= v[3];
-                T1 *= v[4];
-                T2 *= v[5];
+                behind(L0, M0, T0, v[3]);
+                behind(L1, M1, T1, v[4]);
+                behind(L2, M2, T2, v[5]);
             }
         };
         // Four slots are fetched at once: a halo's tile has hundreds, and the
