@@ -1181,12 +1181,18 @@ __global__ __launch_bounds__(64) void k_splat_box(SplatArgs a) {
 //
 // behind: adds a segment's optical depth to (L, M) and gives the transmittance
 // T = exp(-(L - M)).  A depth above 256 (exp(-104) is 0) counts as 256, so an
-// infinite one stays out of the compensation; NaN stays NaN.
+// infinite one stays out of the compensation; NaN stays NaN.  The exponential
+// is 2^-(L log2(e)) with the product's rounding, log2(e)'s own and M put back to
+// first order: a tile's fold is one chain over its segments, and the library's
+// expf doubles it.
 __device__ __forceinline__ void behind(float &L, float &M, float &T, float l) {
 #pragma clang fp contract(off)
     kahan_step(L, M, (l > 256.f ? 256.f : l) - M);
-    T = expf(-L);
-    T = __builtin_fmaf(T, M, T);
+    constexpr float kLog2eLow = 1.925963033500e-8f;  // log2(e) - kLog2e
+    const float p = L * kLog2e;
+    const float r = __builtin_fmaf(L, kLog2eLow, __builtin_fmaf(L, kLog2e, -p));
+    T = __builtin_amdgcn_exp2f(-p);
+    T = __builtin_fmaf(T, __builtin_fmaf(-r, 0.6931471805599453f, M), T);
 }
 
 template <int T, bool ORDERED, bool KAHAN>
