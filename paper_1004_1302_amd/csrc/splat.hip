@@ -1433,7 +1433,11 @@ __global__ void k_store_args(SplatArgs a, SplatArgs *dst) {
     if (threadIdx.x == 0 && blockIdx.x == 0) *dst = a;
 }
 
-// A persistent grid: 8 single-wave workgroups per SIMD, a multiple of 8.
+// A persistent grid: 8 single-wave workgroups per SIMD, a multiple of 8.  Only 6
+// fit at once, so the last quarter's first units start late; but views of up
+// to 8192 units ask no counter.  With the 6144 that fit, 24 views of 1e6
+// particles in four lanes take 4.81 ms instead of 4.08, 5e6 particles on
+// 1024 x 1024 1.25 ms a view instead of 1.27, larger views the same.
 constexpr uint32_t kPersistentGroups = 256 * 4 * 8;
 
 template <int T, bool ORDERED, bool KAHAN, bool GEN>
