@@ -122,12 +122,13 @@ Layout layout(int64_t n, const splotch_camera *cam, const splotch_params *p, uin
     L.scan = take(scan_u32_u64_scratch_bytes(N));
     L.pk1 = take(cap * 4);
     L.pv1 = take(cap * 4);
-    // the sorts' scratch runs on over the slots
-    const size_t slot = 6 * (size_t)L.tile * L.tile * 4;
+    // the sorts' scratch runs on over the slots, which are as large as an
+    // ordered set's for every set
+    const size_t plane = (size_t)L.tile * L.tile * 4;
     L.radix = take(radix_scratch_bytes(std::max<size_t>(L.ordered ? N : 0, (size_t)cap)));
-    take(seg_slots_sure(cap, (uint32_t)p->seg_records) * slot);
+    take(seg_slots_sure(cap, (uint32_t)p->seg_records) * slot_planes(true) * plane);
     L.radix_bytes = o - L.radix;
-    L.max_slots = (o - L.partial) / slot;
+    L.max_slots = (o - L.partial) / (slot_planes(L.ordered) * plane);
     L.total = o;
     return L;
 }

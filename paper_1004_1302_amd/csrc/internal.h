@@ -210,6 +210,8 @@ hipError_t launch_chunk_plan(const uint64_t *off, uint64_t n, uint64_t capacity,
 // segments of at most seg_len records; a tile with one segment writes its
 // pixels directly, a tile with several writes one partial (C, L) per
 // segment that the merge kernel folds front to back.
+// Planes of a partial image: colours, and an ordered set's optical depths.
+__host__ __device__ constexpr int slot_planes(bool ordered) { return ordered ? 6 : 3; }
 struct SplatArgs {
     const Rec *rec;
     const uint32_t *pair_val;
@@ -219,7 +221,7 @@ struct SplatArgs {
     const uint64_t *seg_off;    // [n_tiles + 1] first item of each tile
     const uint64_t *part_off;   // [n_tiles + 1] first partial slot of each multi-segment tile
     const uint32_t *item_tile;  // item -> tile
-    float *partial;             // [slot][6][T*T]: C0 C1 C2 L0 L1 L2 (optical depths)
+    float *partial;             // [slot][slot_planes][T*T]: C0 C1 C2, ordered sets also L0 L1 L2
     uint64_t max_slots;         // partial slots in the buffer
     uint64_t max_items;         // entries of item_tile
     const uint32_t *seg_len;    // device: records per segment for this pass
@@ -251,7 +253,7 @@ constexpr int kSplatBox = 0, kSplatRows = 1, kSplatLists = 2;
 // Without one (seg_min = 0) the least length follows the pairs: a list is
 // walked record by record, so where a pass has fewer items than the GPU has
 // room for, its longest list is what it waits for.  A segment then holds
-// 1 / seg_fill(nt) of the pairs (8192 waves of 8x8 blocks, the GPU's 256 CUs
+// 1 / 2^seg_fill_bits(nt) of the pairs (8192 waves of 8x8 blocks, the GPU's 256 CUs
 // hold 6144), from 128 records (below, a segment's setup and its partial image
 // cost what the shorter walk saves) to 1024 (or nt): the splat of 1e5
 // particles at 256 x 256 pixels takes 18 us, 74 with 1024 as the least.
@@ -262,14 +264,17 @@ struct SegRule {
     uint32_t seg_min;  // the caller's least records per segment, 0 = by the pairs
     uint64_t slots;    // partial images a pass may use beyond seg_slots_sure
 };
-__host__ __device__ inline uint64_t seg_fill(uint32_t nt) { return 524288u / nt; }
+// (the device works these out without a division wherever the rule's length
+// fits; nt is a power of two)
+__host__ __device__ inline int seg_fill_bits(uint32_t nt) { return 19 - __builtin_ctz(nt); }
 __host__ __device__ inline uint32_t seg_len_rule(uint64_t npairs, uint32_t nt, uint32_t seg_min) {
     uint64_t s = (npairs + kSegTarget - 1) / kSegTarget;
     if (seg_min) {
         if (s < seg_min) s = seg_min;
         s = (s + nt - 1) / nt * nt;
     } else {
-        uint64_t m = (npairs + seg_fill(nt) - 1) / seg_fill(nt);
+        const int fill = seg_fill_bits(nt);
+        uint64_t m = (npairs + (1ull << fill) - 1) >> fill;
         const uint64_t high = nt > kSegHigh ? nt : kSegHigh;
         m = m < kSegLow ? kSegLow : (m > high ? high : m);
         if (s < m) s = m;
@@ -281,7 +286,9 @@ __host__ __device__ inline uint32_t seg_len_rule(uint64_t npairs, uint32_t nt, u
 // of segments of seg_min (0: kSegHigh) records.  A tile of L > s records has
 // ceil(L / s) < 2 L / s segments of s, so a pass uses fewer than 2 npairs / s.
 __host__ __device__ inline uint64_t seg_slots_sure(uint64_t npairs, uint32_t seg_min) {
-    const uint64_t n = 2 * (npairs / (seg_min ? seg_min : kSegHigh)) + 2;
+    uint64_t n = npairs / kSegHigh;
+    if (seg_min) n = npairs / seg_min;
+    n = 2 * n + 2;
     return n < 2 * kSegTarget ? n : 2 * kSegTarget;
 }
 // Partial images a pass of npairs may use, and the least segment length whose
@@ -294,9 +301,10 @@ __host__ __device__ inline uint32_t seg_len_fits(uint64_t npairs, const SegRule 
     const uint32_t low = seg_len_rule(npairs, r.nt, r.seg_min);
     if (r.seg_min) return low;
     const uint64_t slots = seg_slots(npairs, r);
+    if (low * slots >= 2 * npairs) return low;
     uint64_t s = (2 * npairs + slots - 1) / slots;
     s = (s + 63) / 64 * 64;
-    return s > low ? (uint32_t)(s < 0x7FFFFFFFull ? s : 0x7FFFFFFFull) : low;
+    return (uint32_t)(s < 0x7FFFFFFFull ? s : 0x7FFFFFFFull);
 }
 // Segment bookkeeping for one pass: segment length (from the pair count,
 // host value or device pointer), counts per tile, their scans and the

@@ -252,6 +252,11 @@ __device__ __forceinline__ void finish(Px &p, float &T0, float &T1, float &T2) {
     }
 }
 
+// A segment's optical depth as its partial image holds it: a depth above 256
+// (exp(-104) is 0) counts as 256, so that an infinite one stays out of the
+// merge's compensated sum; NaN stays NaN.
+__device__ __forceinline__ float segment_depth(float L) { return L > 256.f ? 256.f : L; }
+
 constexpr uint32_t kRun = 2;  // consecutive items per XCD run
 
 // Final pixel value: composite over the incoming image when accumulating.
@@ -539,14 +544,14 @@ __global__ __launch_bounds__(T *T) void k_splat_lists(SplatArgs a) {
     if (nseg == 1) {
         write_pixel<ORDERED>(a, i, j, px.C0, px.C1, px.C2, T0, T1, T2);
     } else if (a.part_off[tile] + seg < a.max_slots) {
-        float *slot = a.partial + (size_t)(a.part_off[tile] + seg) * 6 * NT;
+        float *slot = a.partial + (size_t)(a.part_off[tile] + seg) * slot_planes(ORDERED) * NT;
         slot[0 * NT + tid] = px.C0;
         slot[1 * NT + tid] = px.C1;
         slot[2 * NT + tid] = px.C2;
         if (ORDERED) {
-            slot[3 * NT + tid] = px.L0;
-            slot[4 * NT + tid] = px.L1;
-            slot[5 * NT + tid] = px.L2;
+            slot[3 * NT + tid] = segment_depth(px.L0);
+            slot[4 * NT + tid] = segment_depth(px.L1);
+            slot[5 * NT + tid] = segment_depth(px.L2);
         }
     }
 }
@@ -817,14 +822,14 @@ __device__ __forceinline__ void rows_unit(const SplatArgs &a, uint32_t item, uin
         write_pixel<ORDERED>(a, i, j, px.C0, px.C1, px.C2, T0, T1, T2);
     } else if (a.part_off[tile] + seg < a.max_slots) {
         const int p = (j - ty0) * T + (i - tx0);
-        float *slot = a.partial + (size_t)(a.part_off[tile] + seg) * 6 * NT;
+        float *slot = a.partial + (size_t)(a.part_off[tile] + seg) * slot_planes(ORDERED) * NT;
         slot[0 * NT + p] = px.C0;
         slot[1 * NT + p] = px.C1;
         slot[2 * NT + p] = px.C2;
         if (ORDERED) {
-            slot[3 * NT + p] = px.L0;
-            slot[4 * NT + p] = px.L1;
-            slot[5 * NT + p] = px.L2;
+            slot[3 * NT + p] = segment_depth(px.L0);
+            slot[4 * NT + p] = segment_depth(px.L1);
+            slot[5 * NT + p] = segment_depth(px.L2);
         }
     }
 }
@@ -1159,14 +1164,14 @@ __global__ __launch_bounds__(64) void k_splat_box(SplatArgs a) {
         if (nseg == 1) {
             write_pixel<ORDERED>(a, tx0 + x, ty0 + y, C0, C1, C2, T0, T1, T2);
         } else if (a.part_off[tile] + seg < a.max_slots) {
-            float *slot = a.partial + (size_t)(a.part_off[tile] + seg) * 6 * NT;
+            float *slot = a.partial + (size_t)(a.part_off[tile] + seg) * slot_planes(ORDERED) * NT;
             slot[0 * NT + p] = C0;
             slot[1 * NT + p] = C1;
             slot[2 * NT + p] = C2;
             if (ORDERED) {
-                slot[3 * NT + p] = px.L0;
-                slot[4 * NT + p] = px.L1;
-                slot[5 * NT + p] = px.L2;
+                slot[3 * NT + p] = segment_depth(px.L0);
+                slot[4 * NT + p] = segment_depth(px.L1);
+                slot[5 * NT + p] = segment_depth(px.L2);
             }
         }
     }
@@ -1180,14 +1185,13 @@ __global__ __launch_bounds__(64) void k_splat_box(SplatArgs a) {
 // rounded transmittances would gain 2^-24 with each (1e-5 behind 1024).
 //
 // behind: adds a segment's optical depth to (L, M) and gives the transmittance
-// T = exp(-(L - M)).  A depth above 256 (exp(-104) is 0) counts as 256, so an
-// infinite one stays out of the compensation; NaN stays NaN.  The exponential
+// T = exp(-(L - M)).  The exponential
 // is 2^-(L log2(e)) with the product's rounding, log2(e)'s own and M put back to
 // first order: a tile's fold is one chain over its segments, and the library's
 // expf doubles it.
 __device__ __forceinline__ void behind(float &L, float &M, float &T, float l) {
 #pragma clang fp contract(off)
-    kahan_step(L, M, (l > 256.f ? 256.f : l) - M);
+    kahan_step(L, M, l - M);
     constexpr float kLog2eLow = 1.925963033500e-8f;  // log2(e) - kLog2e
     const float p = L * kLog2e;
     const float r = __builtin_fmaf(L, kLog2eLow, __builtin_fmaf(L, kLog2e, -p));
@@ -1209,7 +1213,8 @@ __global__ __launch_bounds__(T *T < 1024 ? T *T : 1024) void k_merge(SplatArgs a
         float C0 = 0.f, C1 = 0.f, C2 = 0.f, K0 = 0.f, K1 = 0.f, K2 = 0.f;
         float T0 = 1.f, T1 = 1.f, T2 = 1.f;
         float L0 = 0.f, L1 = 0.f, L2 = 0.f, M0 = 0.f, M1 = 0.f, M2 = 0.f;
-        const float *slot = a.partial + (size_t)a.part_off[tile] * 6 * NT + p;
+        constexpr int NV = slot_planes(ORDERED);
+        const float *slot = a.partial + (size_t)a.part_off[tile] * NV * NT + p;
         auto over = [&](const float *v) {
             add_term<ORDERED, KAHAN>(C0, K0, T0, v[0]);
             add_term<ORDERED, KAHAN>(C1, K1, T1, v[1]);
@@ -1222,18 +1227,17 @@ __global__ __launch_bounds__(T *T < 1024 ? T *T : 1024) void k_merge(SplatArgs a
         };
         // Four slots are fetched at once: a halo's tile has hundreds, and the
         // fold waited for each in turn (109 us of a 1e7-particle frame, now 52).
-        constexpr int NV = ORDERED ? 6 : 3;
         uint32_t s = 0;
-        for (; s + 4 <= nseg; s += 4, slot += 4 * 6 * NT) {
+        for (; s + 4 <= nseg; s += 4, slot += 4 * NV * NT) {
             float v[4][NV];
 #pragma unroll
             for (int q = 0; q < 4; ++q)
 #pragma unroll
-                for (int k = 0; k < NV; ++k) v[q][k] = slot[(q * 6 + k) * NT];
+                for (int k = 0; k < NV; ++k) v[q][k] = slot[(q * NV + k) * NT];
 #pragma unroll
             for (int q = 0; q < 4; ++q) over(v[q]);
         }
-        for (; s < nseg; ++s, slot += 6 * NT) {
+        for (; s < nseg; ++s, slot += NV * NT) {
             float v[NV];
 #pragma unroll
             for (int k = 0; k < NV; ++k) v[k] = slot[k * NT];
@@ -1276,13 +1280,19 @@ __global__ __launch_bounds__(1024) void k_segments_small(
     // about half the bound, so lengths between the rule's and the sure one are
     // tried on the lists themselves (at most 10, only where the rule's does not
     // surely fit).
+    auto tile_len = [&](uint32_t t) {
+        const uint32_t q = t < n_tiles ? t : n_tiles - 1;
+        return te[q] - ts[q];
+    };
+    uint32_t next = tile_len(threadIdx.x);
     const uint32_t fits = seg_len_fits(np, rule);
     uint32_t seg_len = seg_len_rule(np, rule.nt, rule.seg_min);
     while (seg_len < fits) {
-        uint32_t m = 0;
-        for (uint32_t t = threadIdx.x; t < n_tiles; t += 1024) {
-            const uint32_t len = te[t] - ts[t];
+        uint32_t m = 0, len = next;
+        for (uint32_t t = threadIdx.x; t < n_tiles;) {
             if (len > seg_len) m += (len + seg_len - 1) / seg_len;
+            t += 1024;
+            if (t < n_tiles) len = te[t] - ts[t];
         }
         for (int o = 32; o > 0; o >>= 1) m += (uint32_t)__shfl_xor((int)m, o, 64);
         if (lane == 0) s_m[wave] = m;
@@ -1292,16 +1302,11 @@ __global__ __launch_bounds__(1024) void k_segments_small(
         for (uint32_t k = 0; k < 16; ++k) used += s_m[k];
         __syncthreads();
         if (used <= seg_slots(np, rule)) break;
-        const uint32_t next = (seg_len + seg_len / 4 + 63) / 64 * 64;
-        seg_len = next < fits ? next : fits;
+        const uint32_t longer = (seg_len + seg_len / 4 + 63) / 64 * 64;
+        seg_len = longer < fits ? longer : fits;
     }
     if (threadIdx.x == 0) *seg_len_out = seg_len;
     uint64_t cn = 0, cm = 0;  // items and partial slots of the tiles before
-    auto tile_len = [&](uint32_t t) {
-        const uint32_t q = t < n_tiles ? t : n_tiles - 1;
-        return te[q] - ts[q];
-    };
-    uint32_t next = tile_len(threadIdx.x);
     for (uint32_t base = 0; base < n_tiles; base += 1024) {
         const uint32_t t = base + threadIdx.x;
         uint32_t n = 0, m = 0;
