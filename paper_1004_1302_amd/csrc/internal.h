@@ -116,6 +116,9 @@ hipError_t launch_scan_u32_u64(const uint32_t *in, uint64_t *out, size_t n, void
 // In-place exclusive scan of n uint32 values.
 size_t scan_u32_scratch_bytes(size_t n);
 hipError_t launch_scan_u32(uint32_t *data, size_t n, void *scratch, hipStream_t s);
+// Exclusive scan of the bits set in n words (the same scratch).
+hipError_t launch_scan_bits(const uint32_t *words, uint32_t *out, size_t n, void *scratch,
+                            hipStream_t s);
 
 // Stable LSD radix sort of (key, value) pairs on bits [0, bits) of
 // key - bias (unsigned; keys below bias or at or above bias + 2^bits are

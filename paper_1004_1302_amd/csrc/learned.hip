@@ -82,9 +82,10 @@ __global__ void k_decimate_mark(Perm perm, uint64_t keep_count, uint32_t *bits) 
     }
 }
 
-__global__ void k_decimate_count(const uint32_t *bits, uint64_t words, uint32_t *pos) {
+// Every index kept (keep = 1): nothing to evaluate.
+__global__ void k_decimate_all(uint64_t n, uint64_t words, uint32_t *bits) {
     const uint64_t w = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (w < words) pos[w] = (uint32_t)__popc(bits[w]);
+    if (w < words) bits[w] = n - 32 * w >= 32 ? ~0u : (1u << (uint32_t)(n - 32 * w)) - 1u;
 }
 
 struct DecArgs {
@@ -366,15 +367,17 @@ splotch_status splotch_decimate(const splotch_particles *in, int32_t keep, uint6
     perm.key = mix64(seed ^ 0xD1B54A32D192ED03ull);
     perm.half = 1;
     while ((1ull << (2 * perm.half)) < n) ++perm.half;
-    L_TRY(launch_fill_u32(bits, 0u, words, s));
-    // at most 8 waves a SIMD, which go through the images in turns
-    const unsigned mark = (unsigned)std::min<uint64_t>((m + 255) / 256, 2048);
-    hipLaunchKernelGGL(k_decimate_mark, dim3(mark), dim3(256), 0, s, perm, m, bits);
-    L_TRY(hipGetLastError());
     const unsigned grid = (unsigned)((words + kDecWords - 1) / kDecWords);
-    hipLaunchKernelGGL(k_decimate_count, dim3(grid), dim3(kDecWords), 0, s, bits, words, pos);
+    if (m == n) {
+        hipLaunchKernelGGL(k_decimate_all, dim3(grid), dim3(kDecWords), 0, s, n, words, bits);
+    } else {
+        L_TRY(launch_fill_u32(bits, 0u, words, s));
+        // at most 8 waves a SIMD, which go through the images in turns
+        const unsigned mark = (unsigned)std::min<uint64_t>((m + 255) / 256, 2048);
+        hipLaunchKernelGGL(k_decimate_mark, dim3(mark), dim3(256), 0, s, perm, m, bits);
+    }
     L_TRY(hipGetLastError());
-    L_TRY(launch_scan_u32(pos, words, scratch, s));
+    L_TRY(launch_scan_bits(bits, pos, words, scratch, s));
     DecArgs a;
     a.in = *in;
     a.out = *out;

@@ -76,6 +76,15 @@ struct LoadPlain {
     __device__ __forceinline__ uint32_t look(TI) const { return 0u; }
     __device__ __forceinline__ TI finish(TI r, uint32_t) const { return r; }
 };
+// The bits set in each word.
+struct LoadBits {
+    const uint32_t *p;
+    __device__ __forceinline__ uint32_t raw(size_t i) const { return p[i]; }
+    __device__ __forceinline__ uint32_t look(uint32_t) const { return 0u; }
+    __device__ __forceinline__ uint32_t finish(uint32_t v, uint32_t) const {
+        return (uint32_t)__popc(v);
+    }
+};
 struct LoadTaggedCount {
     const uint32_t *order, *cnt;
     __device__ __forceinline__ uint32_t raw(size_t i) const { return order[i]; }
@@ -578,6 +587,11 @@ hipError_t launch_scan_tagged_counts(const uint32_t *order, const uint32_t *cnt,
 
 size_t scan_u32_scratch_bytes(size_t n) {
     return align_up(scan_scratch_words(n) * sizeof(uint32_t), 256);
+}
+
+hipError_t launch_scan_bits(const uint32_t *words, uint32_t *out, size_t n, void *scratch,
+                            hipStream_t s) {
+    return scan_impl<LoadBits, uint32_t>(LoadBits{words}, out, n, nullptr, scratch, s);
 }
 
 hipError_t launch_scan_u32(uint32_t *data, size_t n, void *scratch, hipStream_t s) {
