@@ -1179,16 +1179,18 @@ __global__ __launch_bounds__(64) void k_splat_box(SplatArgs a) {
 
 // Fold the partial (C, L) of a multi-segment tile front to back:
 // C += exp(-L) C_s, L += L_s (the associative "over"); a plain sum when
-// nothing absorbs.  The optical depths are summed compensated and their
+// nothing absorbs.  Colours are added compensated here for frames without
+// compensated sums too: their error would grow with the number of segments,
+// which is not theirs to choose.  (Where such a frame's sum is infinite or NaN,
+// the plain one counts: the compensation of an infinity is NaN.)  The optical depths are summed compensated and their
 // exponential is taken of the sum, so the transmittance behind any number of
 // segments carries the error of one exponential; a product of the segments'
 // rounded transmittances would gain 2^-24 with each (1e-5 behind 1024).
 //
 // behind: adds a segment's optical depth to (L, M) and gives the transmittance
-// T = exp(-(L - M)).  The exponential
-// is 2^-(L log2(e)) with the product's rounding, log2(e)'s own and M put back to
-// first order: a tile's fold is one chain over its segments, and the library's
-// expf doubles it.
+// T = exp(-(L - M)).  The exponential is 2^-(L log2(e)) with the product's
+// rounding, log2(e)'s own and M put back to first order: a tile's fold is one
+// chain over its segments, and the library's expf doubles it.
 __device__ __forceinline__ void behind(float &L, float &M, float &T, float l) {
 #pragma clang fp contract(off)
     kahan_step(L, M, l - M);
@@ -1211,14 +1213,20 @@ __global__ __launch_bounds__(T *T < 1024 ? T *T : 1024) void k_merge(SplatArgs a
     for (int p = threadIdx.x; p < NT; p += blockDim.x) {
         const int i = tx * T + (p % T), j = ty * T + (p / T);
         float C0 = 0.f, C1 = 0.f, C2 = 0.f, K0 = 0.f, K1 = 0.f, K2 = 0.f;
+        float P0 = 0.f, P1 = 0.f, P2 = 0.f;  // plain sums
         float T0 = 1.f, T1 = 1.f, T2 = 1.f;
         float L0 = 0.f, L1 = 0.f, L2 = 0.f, M0 = 0.f, M1 = 0.f, M2 = 0.f;
         constexpr int NV = slot_planes(ORDERED);
         const float *slot = a.partial + (size_t)a.part_off[tile] * NV * NT + p;
         auto over = [&](const float *v) {
-            add_term<ORDERED, KAHAN>(C0, K0, T0, v[0]);
-            add_term<ORDERED, KAHAN>(C1, K1, T1, v[1]);
-            add_term<ORDERED, KAHAN>(C2, K2, T2, v[2]);
+            if (!KAHAN) {
+                add_term<ORDERED, false>(P0, K0, T0, v[0]);
+                add_term<ORDERED, false>(P1, K1, T1, v[1]);
+                add_term<ORDERED, false>(P2, K2, T2, v[2]);
+            }
+            add_term<ORDERED, true>(C0, K0, T0, v[0]);
+            add_term<ORDERED, true>(C1, K1, T1, v[1]);
+            add_term<ORDERED, true>(C2, K2, T2, v[2]);
             if (ORDERED) {
                 behind(L0, M0, T0, v[3]);
                 behind(L1, M1, T1, v[4]);
@@ -1242,6 +1250,11 @@ __global__ __launch_bounds__(T *T < 1024 ? T *T : 1024) void k_merge(SplatArgs a
 #pragma unroll
             for (int k = 0; k < NV; ++k) v[k] = slot[k * NT];
             over(v);
+        }
+        if (!KAHAN) {
+            C0 = fabsf(C0) <= 3.40282347e38f ? C0 : P0;
+            C1 = fabsf(C1) <= 3.40282347e38f ? C1 : P1;
+            C2 = fabsf(C2) <= 3.40282347e38f ? C2 : P2;
         }
         write_pixel<ORDERED>(a, i, j, C0, C1, C2, T0, T1, T2);
     }

@@ -61,3 +61,28 @@ def test_opaque_segments(rho):
         got = image.cpu().numpy()
         assert np.isfinite(got).all()
         assert got.min() == 1.0
+
+
+@pytest.mark.parametrize("variant", [1, 2, 3])
+@pytest.mark.parametrize("tile,seg", [(8, 64), (8, 0)])
+def test_plain_sums_behind_many_segments(tile, seg, variant):
+    """A frame without compensated sums: each of 65,536 additive particles adds
+    (2^16 + 341) 2^-29 to one pixel, so the sums of 64 and of 128 are exact and
+    only joining the segments can round.  The joins are compensated: 2^-23 in
+    all (plain ones are off by 1e-5).  A sum that overflows is infinite."""
+    import torch
+    cam = synth.ortho_unit_square(64, 64)
+    light = (2 ** 16 + 341) * 2.0 ** -29
+    fill = lambda v: torch.full((N,), v, dtype=torch.float32, device="cuda")  # noqa: E731
+    parts = dict(x=fill(36.5 / 64), y=fill(35.5 / 64), z=fill(0.5), h=fill(0.6 / 64),
+                 value=fill(0.0), rho0=fill(light))
+    pal = torch.ones((2, 3), device="cuda")
+
+    def image():
+        img = B.render(parts, cam, pal, [synth.Species(vmin=0.0, vmax=1.0)], tile=tile,
+                       seg_records=seg, splat_variant=variant)
+        return img.cpu().numpy().astype(np.float64)
+
+    assert abs(image().max(axis=(1, 2)) / (N * light) - 1.0).max() <= 2.0 ** -23
+    parts["rho0"].fill_(3.0e38)
+    assert not np.isnan(image()).any() and np.isinf(image()).any()
