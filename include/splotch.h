@@ -186,7 +186,10 @@ typedef struct splotch_params {
                             SPLOTCH_E_INVALID_ARG */
     int32_t seg_records; /* least records per tile-list segment (one workgroup
                             each); 0 = 128 to 1024 (64 px tiles: to 4096) by
-                            the number of pairs.  Long lists are cut into segments
+                            the number of pairs, longer where the workspace
+                            has no room for so many partial images (which does
+                            not differ between workspaces of the default size
+                            and more).  Long lists are cut into segments
                             whose partial (C, L) are merged front to back:
                             this changes speed and, within rounding, how a
                             tile's sums are associated. */
@@ -313,9 +316,10 @@ splotch_status splotch_render_static(const splotch_particles *particles,
  * the combination happens on the device).  host: the particle set in host
  * memory (the same fields as splotch_particles, host pointers; pinned
  * memory lets the copies overlap the work); n may exceed 2^32.  The set is
- * copied to the device `subset` particles at a time, on a library-owned
- * stream (default priority), into two staging buffers, overlapped with the
- * work on params->stream.
+ * copied to the device `subset` particles at a time, on two library-owned
+ * streams by turns (default priority), into two staging buffers, overlapped
+ * with the work on params->stream.  A call that returns an error has ended its
+ * copies.
  *   - Additive-only sets: each subset is rendered and added into the image.
  *   - With an ORDERED species: a first pass projects every subset and
  *     histograms the depth keys (top 20 bits of the binary32 depth image,

@@ -139,7 +139,8 @@ bool fit_capacity(int64_t n, const splotch_camera *cam, const splotch_params *p,
     Layout L0 = layout(n, cam, p, 1);
     if (L0.total > bytes) return false;
     uint64_t lo = 1, hi = kMaxPairCap;
-    // per pair: 16 bytes plus about 0.26 bytes of radix scratch
+    // at least 16 bytes a pair and about 0.26 of radix scratch (slots for
+    // partial images come on top: from 3 bytes for 8 px tiles to 192 for 64)
     uint64_t guess = (uint64_t)((bytes - L0.total) / 16.3);
     hi = std::min<uint64_t>(hi, guess + 4096);
     while (lo < hi) {

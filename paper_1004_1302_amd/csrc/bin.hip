@@ -91,11 +91,13 @@ __global__ __launch_bounds__(kThreads) void k_emit(EmitArgs a) {
 // box in k_emit's order (rows bottom to top, tiles left to right).  Every
 // lane then does the same work however unevenly the tile counts spread,
 // and each store writes consecutive slots.  Split particles are left out
-// of the run (their slots are written by k_emit_split) and queued in the
-// workgroup's own part of the split list, counted in LDS: a counter shared
-// by the whole grid would take one device-scope atomic per queued particle
-// or wave, and those are serialised beyond the XCDs' L2 caches.  Used without a tile
-// mask, where a particle's t-th pair is the t-th tile of its box.
+// of the run (their slots are written by k_emit_split), listed in LDS and
+// queued together.  Up to 4096 workgroups append them to one dense queue, one
+// device-scope atomic a workgroup (launch_emit says why there); beyond, such
+// atomics on one counter, serialised past the XCDs' L2 caches, cost more
+// than a scan, and a workgroup writes its own part of the split list and its
+// count.  Used without a tile mask, where a particle's t-th pair is the t-th
+// tile of its box.
 __global__ __launch_bounds__(kThreads) void k_emit_waves(EmitArgs a) {
     __shared__ uint32_t s_first[kThreads];  // first slot in the wave's run
     __shared__ uint32_t s_off[kThreads];    // first slot, from the wave's first pair

@@ -1,6 +1,7 @@
 // Device-wide exclusive scans and a stable LSD radix sort of (key, value)
-// pairs, written for wave64: 256-thread workgroups, 4096 keys per
-// workgroup tile, 8-bit digits.
+// pairs, written for wave64: 256-thread workgroups, 1024 keys per workgroup
+// tile for sorts of up to 2^20 keys and 4096 beyond (radix_sort_pairs), digits
+// of 7 or 8 bits.
 //
 // Each radix pass is reduce-then-scan: a histogram kernel counts digits per
 // tile (digit-major, so one exclusive scan yields every tile's output
@@ -68,7 +69,8 @@ __device__ __forceinline__ int pad(int i) { return i + (i >> 4); }
 // issues all of its streaming loads, then all of its dependent ones, before it
 // waits.  The dependent loads are unconditional (entry 0 where the tag has the
 // count): under a condition each was waited for before the next (1e7 counts: sums
-// 23 us and scan 28, now 18 and 27; 1e6: 7.6 and 7.2, now 5.7 and 6.3).
+// 23 us and scan 28 instead of 18 and 27; 1e6: 7.6 and 7.2 instead of 5.7 and
+// 6.3).
 template <typename TI>
 struct LoadPlain {
     const TI *p;

@@ -1233,8 +1233,9 @@ __global__ __launch_bounds__(T *T < 1024 ? T *T : 1024) void k_merge(SplatArgs a
                 behind(L2, M2, T2, v[5]);
             }
         };
-        // Four slots are fetched at once: a halo's tile has hundreds, and the
-        // fold waited for each in turn (109 us of a 1e7-particle frame, now 52).
+        // Four slots are fetched at once: a halo's tile has hundreds, and a
+        // fold that waits for each in turn takes 109 us of a 1e7-particle frame
+        // instead of 52.
         uint32_t s = 0;
         for (; s + 4 <= nseg; s += 4, slot += 4 * NV * NT) {
             float v[4][NV];
@@ -1277,9 +1278,9 @@ __global__ void k_seg_count(const uint32_t *ts, const uint32_t *te, uint32_t n_t
 // The same for at most kOneGroupTiles tiles in one workgroup, with the scans
 // and the item map: one launch instead of four (a launch that follows
 // another takes about 5 us here, this kernel 4 to 15).  A wave writes the items
-// of a tile with many segments together: one lane storing the thousands of a
-// halo's tile one after another held the others up (34 us for 1e7 particles of
-// 1000 halos on 1920x1080, now 24).
+// of a tile with many segments together: one lane that stores the thousands of
+// a halo's tile one after another holds the others up (1e7 particles of 1000
+// halos on 1920x1080: 34 us instead of 24).
 constexpr uint32_t kOneGroupTiles = 8192;
 constexpr uint32_t kOwnItems = 8;  // items a lane writes by itself
 __global__ __launch_bounds__(1024) void k_segments_small(

@@ -14,9 +14,9 @@
 // image (C + T I_in).  Per-species automatic value ranges are taken over
 // the whole set in the first pass and passed to every slab render.
 //
-// Host-to-device copies run on a library-owned copy stream into two staging
-// buffers, overlapped with the projection, compaction and render of the
-// previous subset on the caller's stream.
+// Host-to-device copies run on two library-owned copy streams by turns into
+// two staging buffers, overlapped with the projection, compaction and render
+// of the previous subset on the caller's stream.
 #include <string.h>
 
 #include <algorithm>
