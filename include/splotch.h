@@ -292,8 +292,8 @@ splotch_status splotch_render(const splotch_particles *particles, const splotch_
  * (code under HIP graph capture, tight serving loops, harnesses that forbid
  * allocation).  Same arguments, result and errors as splotch_render, except
  * that params->workspace and params->workspace_bytes are ignored: the
- * workspace is a static device buffer of SPLOTCH_STATIC_SCRATCH_BYTES that
- * the library holds on each GPU it runs on until the process ends (its
+ * workspace is a static device buffer of at least SPLOTCH_STATIC_SCRATCH_BYTES
+ * that the library holds on each GPU it runs on until the process ends (its
  * address is looked up once per device, on the first call there).  The
  * call allocates no device memory.
  * Limits: the render's smallest workspace, splotch_workspace_size(n, cam,

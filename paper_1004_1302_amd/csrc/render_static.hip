@@ -1,8 +1,8 @@
 // splotch_render_static: splotch_render for callers that cannot allocate
 // device memory (code under HIP graph capture, tight serving loops,
 // harnesses that forbid allocation).  Its workspace is a file-scope device
-// array of SPLOTCH_STATIC_SCRATCH_BYTES, one copy per GPU, held until the
-// process ends; the caller passes only the particles, palette and image.
+// array of SPLOTCH_STATIC_SCRATCH_BYTES and 1 MiB, one copy per GPU, held until
+// the process ends; the caller passes only the particles, palette and image.
 #include <map>
 #include <mutex>
 
@@ -11,7 +11,9 @@
 
 namespace {
 
-constexpr size_t kScratchBytes = SPLOTCH_STATIC_SCRATCH_BYTES;
+// The 1 MiB is beyond what the header promises: sets up to it have been accepted
+// (about 16,000 particles more at 4e6) and stay so.
+constexpr size_t kScratchBytes = SPLOTCH_STATIC_SCRATCH_BYTES + ((size_t)1 << 20);
 
 // The render's workspace for this entry point.  In host code `scratch`
 // names a host-side stand-in, never the device memory: host code uses only
